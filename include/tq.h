@@ -163,10 +163,11 @@ tq_status tq_dual_gemm_fused_quant(const tq_weight_desc *d, const void *packed, 
 /* Kernels of tq_dual_gemm. */
 typedef enum {
   TQ_KERNEL_DECODE = 0,   /* m <= 16: weight-streaming, H formed in every work-group */
-  TQ_KERNEL_MID = 1,      /* 32-token blocks, K split over wavefronts */
+  TQ_KERNEL_MID = 1,      /* 32- or 64-token blocks, K may be split over wavefronts */
   TQ_KERNEL_LARGE = 2,    /* 128 x 256 blocks, H in the main loop */
   TQ_KERNEL_PREFILL = 3   /* 128 x 256 blocks, H in a separate pass */
-} tq_kernel;
+} tq_kernel;   /* (2 and 3: or the mid kernel's blocks without a split of K where
+                  they take less time; the results are the same bits) */
 
 /* The kernel tq_dual_gemm launches for descriptor d and m tokens (a tq_kernel
  * value), or -1 for a NULL or invalid descriptor or m outside [1, 2^24].
@@ -189,8 +190,9 @@ int tq_dual_gemm_kernel(const tq_weight_desc *d, int m);
  *              tq_kernel value to run (TQ_KERNEL_DECODE needs a decode-sized
  *              m that fits its LDS, TQ_KERNEL_LARGE / TQ_KERNEL_PREFILL need
  *              m > 512, TQ_KERNEL_MID serves any m; TQ_ERR_SHAPE otherwise)
- *   mid_tiles  0: the mid kernel's own choice of 32-column tiles per
- *              work-group; 1, 2 or 4 forces it (TQ_ERR_SHAPE otherwise)
+ *   mid_tiles  0: the mid kernel's own choice of token and column tiles per
+ *              work-group; 1, 2 or 4 forces 32 tokens and that many 32-column
+ *              tiles (TQ_ERR_SHAPE otherwise)
  *   h, sh, qh  all NULL, or all set (r > 0, else TQ_ERR_RANK) to copy the
  *              low-rank intermediate of every token out of the kernel:
  *                h   [m,r] fp32     H before re-quantization

@@ -6,15 +6,25 @@
 // blocks) -- for r <= 64 only where a run is long enough to carry its H pass;
 // past 512 tokens the mid kernel again where the large kernel's blocks would
 // leave most CUs idle.
+#include <algorithm>
+
 #include "tq_kernels.hpp"
 
 namespace tq {
 
-// one round of large-kernel blocks in the mid kernel's cost units, for 64-
-// and 128-wide groups (fitted to measured mid and large times: 164 layer
-// shapes with K 4096-28672, N 1024-14336, r 0-128, M 576-4096, and the
-// LLaMA3 shapes of both group widths)
+// Past 512 tokens, where Y's fp32 sums may be split over K (the mid kernel's
+// plans of one or two column tiles): rounds of 32-token work-groups x (3 + rank
+// tiles + column tiles) below this many units per round of large blocks, for
+// 64- and 128-wide groups.  The line is where callers find it through
+// tq_dual_gemm_kernel, and stays; how each side runs is chosen by time below.
 constexpr int kLargeRound64 = 34, kLargeRound128 = 28;
+int split_units(const GemmArgs &a) {
+  const int rt = a.geo.r_pad32 / 32, ct32 = a.geo.n_pad / 32, n_rb = a.ms / 32;
+  int best = 1 << 30;
+  for (int ct : {1, 2, 4})
+    best = std::min(best, (n_rb * ((ct32 + ct - 1) / ct) + 255) / 256 * (3 + rt + ct));
+  return best;
+}
 // K-groups per prefill work-group run from which it beats the large kernel at r <= 64
 constexpr int kPrefillMinRun = 256;
 
@@ -41,23 +51,45 @@ int choose_kernel(const GemmArgs &a) {
   // at every rank but 0.
   const bool prefill_wins = a.geo.gk == 1 ? a.geo.r_pad32 > 64 || long_run : a.geo.r_pad32 > 0;
   const bool large = blocks <= 256 || !prefill_wins;
-  // Few large blocks leave most CUs idle (a round of them costs about as much
-  // as kLargeRound64 / kLargeRound128 tile-group units of the mid kernel,
-  // whose 32-token blocks fill the CUs at these sizes too): take the cheaper
-  // of the two.
+  // few large blocks leave most CUs idle
   const int rounds = (blocks + 255) / 256;
   const int large_round = a.geo.gk == 1 ? kLargeRound64 : kLargeRound128;
-  const bool mid = large && dual_gemm_mid_cost(a) < rounds * large_round;
+  const bool mid = large && split_units(a) < rounds * large_round;
   if (mid) return kKernelMid;
   return large ? kKernelLarge : kKernelPrefill;
 }
 
+// Time of a large or prefill launch in ns, to compare with the mid kernel's
+// plans that sum Y in the same ascending order: rounds of blocks x a time per
+// 64-wide K block for the large kernel, one H pass and the run's blocks for
+// the prefill kernel (measured at K = 4096 and 14336, N = 4096 and 14336, M =
+// 576 to 4096, within 10 %).
+int64_t block_kernel_ns(const GemmArgs &a, int kernel) {
+  const int m_tiles = (a.m + 127) / 128, n_tiles = (a.geo.n_pad + 255) / 256;
+  const int rt = a.geo.r_pad32 / 32, c = rt == 0 ? 0 : (rt <= 2 ? 1 : 2), g2 = a.geo.gk == 2;
+  const int64_t kg = a.geo.k / 64;
+  if (kernel == kKernelLarge) {
+    constexpr int kBlock[2][3] = {{680, 800, 970}, {460, 740, 760}};
+    return ((int64_t)m_tiles * n_tiles + 255) / 256 * (10000 + kg * kBlock[g2][c]);
+  }
+  constexpr int kPass[3] = {0, 250, 420};
+  const int runs = m_tiles >= 256 ? 1 : 256 / m_tiles, cpw = (n_tiles + runs - 1) / runs;
+  return 6000 + kg * (kPass[c] + (g2 ? 620 : 700) * (int64_t)cpw) * ((m_tiles + 255) / 256);
+}
+
 hipError_t launch_dual_gemm(const GemmArgs &a, hipStream_t s) {
-  switch (choose_kernel(a)) {
+  const int kernel = choose_kernel(a);
+  switch (kernel) {
     case kKernelDecode: return launch_dual_gemm_decode(a, nullptr, s);
-    case kKernelMid: return launch_dual_gemm_mid(a, s);
-    case kKernelLarge: return launch_dual_gemm_large(a, s);
-    default: return launch_dual_gemm_prefill(a, s);
+    case kKernelMid: return launch_dual_gemm_mid(a, false, s);
+    default:
+      // 128 x 256 blocks, or the mid kernel's smaller ones with Y in the same
+      // ascending order where they take less time (few blocks, or a last round
+      // that is nearly empty): LLaMA3-8B q/o_proj, r = 128 in 128-wide groups,
+      // M = 576: 58 -> 43 us
+      if (a.force_kernel < 0 && dual_gemm_mid_ns(a) < block_kernel_ns(a, kernel))
+        return launch_dual_gemm_mid(a, true, s);
+      return kernel == kKernelLarge ? launch_dual_gemm_large(a, s) : launch_dual_gemm_prefill(a, s);
   }
 }
 

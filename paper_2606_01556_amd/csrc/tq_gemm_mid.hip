@@ -3,35 +3,44 @@
 // stage-1 product H = Q(X) Q(L1) kept on chip, its on-the-fly
 // re-quantization, stage 2 Q_H Q(L2) and one epilogue, in one kernel.
 //
-// Work decomposition.  A workgroup of 8 wavefronts owns one block of 32
-// tokens and CT output tiles of 32 columns.  Since every output tile needs
-// all of H for its tokens, each workgroup forms the 32 x r block of H itself.
+// Work decomposition.  A workgroup of 8 wavefronts owns one block of TB
+// 32-token tiles and CT output tiles of 32 columns.  Since every output tile
+// needs all of H for its tokens, each workgroup forms the H of its tokens.
 //  * H wavefronts (wavefronts 0 .. RT-1, RT = r/32 rounded up) each own one
-//    32 x 32 tile of H and walk all K-groups in ascending order, so H and Q_H
-//    are bit-identical to the oracle's.
-//  * the other wavefronts share the residual tile-groups (CT tiles x the
-//    groups of each chunk of K); their partial sums are added in a fixed
-//    order at the end (only Y's fp32 summation order differs from the
-//    oracle's).  Wavefronts on SIMDs without an H wavefront take the larger
-//    shares.
+//    column of TB 32 x 32 tiles of H and walk all K-groups in ascending order,
+//    so H and Q_H are bit-identical to the oracle's.
+//  * the other wavefronts own one column of TB residual tiles each.  Where
+//    there are fewer column tiles than residual wavefronts, NPH wavefronts
+//    share a column and take NPH-th parts of every chunk of K; their partial
+//    sums are added in a fixed order at the end (only Y's fp32 summation order
+//    then differs from the oracle's).
 // Per tile and group (Eq. 2): v_mfma_scale_f32_32x32x64_f8f6f4 returns half
 // of the exact integer group sum (codes as fp8 subnormals), v_mfma_f32_32x32x8
 // f16 twice the exact scale product, and one fma per element applies their
 // product, exactly I * s_x * s_w.
 //
-// Data movement: direct global -> LDS loads (global_load_lds_dwordx4) with
-// explicit wait counts.  K runs in chunks of MCG groups through a ring of D
-// chunk slots, D - 1 chunks ahead.  A slot holds the chunk's raw activation
-// blocks, all its scales and every wavefront's own weight / L1 blocks.  Each
-// wavefront issues one shared load and its own block loads per chunk, so each
-// wait is one constant s_waitcnt.  One chunk ahead, the two least-loaded wavefronts expand the
-// activation codes to fp8 operand bytes, shared by all eight wavefronts.  One
-// workgroup barrier per chunk.
+// Data movement.  A weight or L1 block is the operand of one wavefront alone,
+// so it streams from global memory straight into that wavefront's registers,
+// a chunk of K ahead (raw buffer loads: one instruction each, zeros past K).
+// The activation operands and all scales are shared: K runs in chunks of MCG
+// blocks, which the workgroup loads two chunks ahead into registers and writes
+// one chunk ahead into a double buffer in LDS (the activation codes as fp8
+// operand bytes, expanded there once).  One workgroup barrier per chunk;
+// between barriers the wavefronts run freely, so one wavefront's matrix
+// products overlap another's vector work.
 //
-// Above 512 tokens the activation codes arrive as fp8 operand bytes (two
-// 1 KiB halves per group): each wavefront then issues two shared loads per
-// chunk, and the operands are read from the chunk slot as loaded, with no
-// expansion.
+// What bounds it.  With 32 tokens, the H wavefront of a SIMD: its own stream of
+// ~36 instructions per K block, 110 ns.  (Bound before by its chunk of four
+// blocks: a barrier, an LDS round trip of every operand and ~59 instructions
+// per block; 16 blocks per chunk and operands in registers instead took
+// 4096 -> 4096, r = 64, M = 128 from 19.8 to 13.7 us, 28672 -> 8192, r = 128,
+// M = 32 from 91 to 63 us.)  Where 32-token blocks need more than one round
+// over the CUs, a wavefront takes two token tiles: one weight operand loaded
+// and expanded for both, and H formed once for twice the columns: four
+// tile-groups per SIMD and K block in 310 ns, 4096 -> 12288, r = 64, M = 256
+// from 61.7 to 27.3 us.  Sixteen wavefronts of one tile each instead of eight
+// of two were slower (32 us: 128 registers leave no room to hold a tile's
+// products while the next one's are formed).
 
 #include <type_traits>
 
@@ -45,57 +54,43 @@ typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int MW = 8;                  // wavefronts per workgroup
-constexpr int MCG = 4;                 // K-groups per chunk
 constexpr int M_LDS = 160 * 1024;      // LDS of a CU
 
-template <int RT, int CT, bool FP8>
+// TB token tiles, RT rank tiles, CT column tiles; GK 64-wide blocks per
+// quantization group
+template <int TB, int RT, int CT, int GK>
 struct MCfg {
-  static constexpr int NRW = MW - RT;                  // residual wavefronts
-  static constexpr int NITEM = MCG * CT;               // residual tile-groups per chunk
-  static constexpr int NF_MAX = (NITEM + NRW - 1) / NRW;
-  // activation bytes of a group as loaded: 1 KiB of TQ4 nibbles, or two
-  // 1 KiB halves of fp8 bytes (the operand's split layout)
-  static constexpr int XB = FP8 ? 2048 : 1024;
-  static constexpr int SHL = FP8 ? 2 : 1;              // shared wave loads per wavefront and chunk
-  // scale pieces (16 bytes = 8 fp16) of a chunk: activation, weight, L1
-  static constexpr int NPX = MCG * 4, NPW = MCG * 4 * CT, NPL = MCG * 4 * RT;
-  static constexpr int NP = NPX + NPW + NPL;
-  static constexpr int NSI = (NP + 63) / 64;           // scale wave loads
-  static constexpr int NSH = MCG * SHL + NSI;          // shared wave loads per chunk
-  // chunk slot
-  static constexpr int S_X = 0;                        // MCG raw activation blocks
-  static constexpr int S_SC = MCG * XB;                // scale pieces
-  static constexpr int S_FR = S_SC + NSI * 1024;       // blocks: H (RT x MCG), residual items
-  static constexpr int SLOT = S_FR + (RT * MCG + NITEM) * 1024;
-  // expanded activation operands (TQ4 only): 2 buffers x MCG groups x 2 KiB
-  // of fp8 bytes; fp8 activations are read from the slot as loaded
-  static constexpr int XEB = FP8 ? 0 : MCG * 2048;
-  // stage-2 operands: CT x RB L2 blocks and one scale region
-  static constexpr int RB = (RT + 1) / 2;              // 64-rank blocks (= rank groups)
-  static constexpr int L2B = RT > 0 ? CT * RB * 1024 + 1024 : 0;
-  static constexpr int DFIT = (M_LDS - 2 * XEB - L2B) / SLOT;
-  // the wait for a chunk leaves (D - 2) chunks of loads outstanding, and
-  // vmcnt counts to 63
-  static constexpr int PER_MAX = SHL + (RT > 0 && MCG > NF_MAX ? MCG : NF_MAX);
-  static constexpr int DVM = 63 / PER_MAX + 2;
-  static constexpr int D = DFIT < DVM ? (DFIT > 16 ? 16 : DFIT) : (DVM > 16 ? 16 : DVM);   // chunk slots
-  static constexpr int OFF_XE = D * SLOT;
-  static constexpr int OFF_L2 = OFF_XE + 2 * XEB;
-  static constexpr int LDS = OFF_L2 + L2B;
-  // epilogue (aliases the ring)
+  static constexpr int MCG = TB == 1 ? 16 : 8;          // 64-wide K blocks per chunk
+  static constexpr int NRES = MW - RT;                  // residual wavefronts
+  static constexpr int CI = MCG / GK;                   // quantization groups of a chunk
+  // groups of a chunk per wavefront of a column tile: whole quads (the scale
+  // operands hold four groups), and the wavefronts that share the tile
+  static constexpr int PMAX = NRES / CT;
+  static constexpr int IPC = CI >= 16 && PMAX >= 4 ? CI / 4 : (CI >= 8 && PMAX >= 2 ? CI / 2 : CI);
+  static constexpr int NPH = CI / IPC;
+  static constexpr int NT = TB + RT + CT;               // rows of scale tiles: x, L1, W
+  static constexpr int NP = NT * CI * 4;                // 16-byte scale pieces of a chunk
+  static constexpr int SPT = (NP + 64 * MW - 1) / (64 * MW);   // pieces per thread
+  static constexpr int APW = MCG / MW;                  // activation blocks per wavefront and chunk
+  // chunk buffer: activation operands [TB][MCG] x 2 KiB (two 1 KiB halves),
+  // scales [NT][32][CI] fp16 (a row's groups together: one read per chunk)
+  static constexpr int S_S = TB * MCG * 2048;
+  static constexpr int BUF = (S_S + NP * 16 + 1023) / 1024 * 1024;
+  static constexpr int RB = (RT + 1) / 2;               // 64-rank blocks
+  // epilogue (aliases the chunk buffers)
+  static constexpr int ROWS = 32 * TB;
   static constexpr int HSTR = RT * 32 + 1;
   static constexpr int QSTR = (RB > 0 ? RB : 1) * 64 + 16;
-  static constexpr int E_HS = 0;                                  // [32][HSTR] fp32
-  static constexpr int E_QS = E_HS + 32 * HSTR * 4;               // [32][QSTR] fp8 codes
-  static constexpr int E_SH = E_QS + 32 * QSTR;                   // [RB][32] fp32
-  static constexpr int E_RES = (E_SH + (RB > 0 ? RB : 1) * 128 + 255) / 256 * 256;
-  static constexpr int E_END = E_RES + NITEM * 4096;              // [NITEM][64 lanes][16] fp32
-  static_assert(NSH <= MW * SHL, "SHL shared loads per wavefront and chunk");
-  static_assert(NF_MAX <= 4, "at most four residual items per wavefront and chunk");
-  static_assert(D >= 3, "at least two chunks in flight");
-  static_assert(MCG % 2 == 0 && NRW >= 2, "two expansion wavefronts, MCG / 2 groups each");
+  static constexpr int E_HS = 0;                                  // [ROWS][HSTR] fp32
+  static constexpr int E_QS = (E_HS + ROWS * HSTR * 4 + 15) / 16 * 16;   // [ROWS][QSTR] fp8 codes
+  static constexpr int E_SH = E_QS + ROWS * QSTR;                 // [RB][ROWS] fp32
+  static constexpr int E_RES = (E_SH + (RB > 0 ? RB : 1) * ROWS * 4 + 255) / 256 * 256;
+  // partial sums of the wavefronts ph > 0 of each column: [CT][NPH - 1][TB][64][16] fp32
+  static constexpr int E_END = E_RES + CT * (NPH - 1) * TB * 4096;
+  static constexpr int LDS = E_END > 2 * BUF ? E_END : 2 * BUF;
+  static_assert(CT * NPH <= NRES, "a wavefront per column tile and part of K");
+  static_assert(IPC % 4 == 0, "whole quads");
   static_assert(LDS <= M_LDS, "fits the 160 KiB LDS of a CU");
-  static_assert(E_END <= D * SLOT, "the epilogue fits in the ring");
 };
 
 // Residual rank of wavefront w (w >= RT): wavefronts on SIMDs (w % 4) without
@@ -113,22 +108,10 @@ __host__ __device__ constexpr int res_index(int rt, int w) {
   return -1;
 }
 
-template <int N>
-__device__ __forceinline__ void mwait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt has 6 bits");
-  __builtin_amdgcn_s_waitcnt((N & 0xf) | ((N >> 4) << 14) | (0x7 << 4) | (0xf << 8));
-}
-
-// 16 bytes per lane from addr into LDS at lds + 16 * lane
-__device__ __forceinline__ void mdma(const uint8_t *addr, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(addr), "s"(lds)
-               : "memory");
-}
-
-// the same with a wave-uniform base and a 32-bit lane offset
-__device__ __forceinline__ void mdma_s(uint32_t voff, const uint8_t *sbase, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
-               : "memory");
+// every LDS access of this wavefront so far has completed, then the workgroup
+// barrier (global loads into registers stay in flight across it)
+__device__ __forceinline__ void m_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // a wave-uniform pointer, kept in scalar registers
@@ -139,17 +122,28 @@ __device__ __forceinline__ const uint8_t *m_uniform(const uint8_t *p) {
   return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
 }
 
-__device__ __forceinline__ v8i lds_v8i(const uint8_t *p) {
-  const u32x4 lo = *reinterpret_cast<const u32x4 *>(p);
-  const u32x4 hi = *reinterpret_cast<const u32x4 *>(p + 16);
+// Raw buffer of `bytes` bytes at a wave-uniform address: loads past its end
+// return zeros (and read nothing), so a block past K needs no test.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t m_buffer(const uint8_t *base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(m_uniform(base)), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 m_load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
+}
+
+__device__ __forceinline__ v8i m_join(u32x4 lo, u32x4 hi) {
   return v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
 }
 
-// 2 * s_row * s_col of a 32x32 tile (both scales in k = 0 and k = 4)
-__device__ __forceinline__ v16f m_outer2(uint32_t sa, uint32_t sb) {
+// 2 * s_row * s_col of a 32x32 tile for group J % 4 of four: sa and sb hold the
+// four groups' fp16 scales of the lane's row and column (in k = 0..3 and
+// k = 4..7); all but the group's are cleared in sb, so the other groups' row
+// scales meet zeros
+__device__ __forceinline__ v16f m_outer2(u32x2 sa, u32x2 sb, int j) {
   const v16f z = {0};
-  const u32x2 a2 = {sa, 0u}, b2 = {sb, 0u};
-  return __builtin_amdgcn_mfma_f32_32x32x8f16(__builtin_bit_cast(v4h, a2),
+  const uint32_t w = (j & 2 ? sb.y : sb.x) & (j & 1 ? 0xffff0000u : 0xffffu);
+  const u32x2 b2 = j & 2 ? u32x2{0u, w} : u32x2{w, 0u};
+  return __builtin_amdgcn_mfma_f32_32x32x8f16(__builtin_bit_cast(v4h, sa),
                                               __builtin_bit_cast(v4h, b2), z, 0, 0, 0);
 }
 
@@ -165,15 +159,15 @@ __device__ __forceinline__ v16f m_codes_half_acc(v8i a, v8i b, v16f c) {
                                                          kScale2p9);
 }
 
-template <int RT, int CT, bool FP8>
-__global__ __launch_bounds__(64 * MW, 1) void dual_gemm_mid_kernel(GemmArgs a, int n_rb) {
-  using C = MCfg<RT, CT, FP8>;
-  constexpr int D = C::D;
+template <int TB, int RT, int CT, int GK, bool FP8>
+__global__ __launch_bounds__(64 * MW, 2) void dual_gemm_mid_kernel(GemmArgs a, int n_rb) {
+  using C = MCfg<TB, RT, CT, GK>;
+  constexpr int MCG = C::MCG;
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const Geometry &geo = a.geo;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int KG = geo.k / kGroup, NCH = (KG + MCG - 1) / MCG;
+  const int KG = geo.k / kGroup, KQ = KG / GK, NCH = (KG + MCG - 1) / MCG;
   const int ct32 = geo.n_pad / 32;
   const int m = a.m, ms = a.ms;
 
@@ -187,391 +181,341 @@ __global__ __launch_bounds__(64 * MW, 1) void dual_gemm_mid_kernel(GemmArgs a, i
     logical = (x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per) + s;
   }
   const int cb = logical / n_rb, tb = logical % n_rb;   // column block, token block
-  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
 
-  const uint8_t *xc = reinterpret_cast<const uint8_t *>(a.xc) + (int64_t)tb * KG * C::XB;
-  const uint8_t *xs = reinterpret_cast<const uint8_t *>(a.xs);
-  const uint8_t *wcodes = a.packed + geo.off_w;
-  const uint8_t *wscales = a.packed + geo.off_ws;
-  const uint8_t *l1codes = a.packed + geo.off_l1;
-  const uint8_t *l1scales = a.packed + geo.off_l1s;
-  const uint8_t *l2codes = a.packed + geo.off_l2;
-  const uint8_t *l2scales = a.packed + geo.off_l2s;
-
-  // ---- this wavefront's shared loads: lane reads base + g * stride ----
-  // Shared load sh < MCG * SHL is half sh % SHL of the activation block of
-  // group sh / SHL of the chunk, the rest are scale pieces 64 s + lane.
-  // Wavefront w issues loads w and (fp8) w + MW, modulo NSH: loads past NSH
-  // repeat one (same bytes, same place).  A scale row serves gk = group / 64
-  // blocks (shift = 1 for 128-wide groups): block g reads row g >> shift, so
-  // each block of a chunk slot holds its group's scales.
-  const int gk = geo.gk;
-  struct Shared {
-    const uint8_t *base;
-    uint32_t stride, dst;
-    int gi, shift;
-  };
-  auto shared_load = [&](int sh) {
-    Shared L;
-    L.shift = 0;
-    if (sh < MCG * C::SHL) {
-      const int gi = sh / C::SHL, half = sh % C::SHL;
-      L.base = xc + half * 1024 + lane * 16;
-      L.stride = C::XB;
-      L.gi = gi;
-      L.dst = C::S_X + gi * C::XB + half * 1024;
-    } else {
-      L.shift = gk - 1;
-      const int s = sh - MCG * C::SHL;
-      const int p0 = 64 * s + lane;
-      const int p = p0 < C::NP ? p0 : 0;
-      L.dst = C::S_SC + s * 1024;
-      if (p < C::NPX) {
-        L.gi = p / 4;
-        L.base = xs + (int64_t)(32 * tb + 8 * (p % 4)) * 2;
-        L.stride = (uint32_t)ms * 2;
-      } else if (p < C::NPX + C::NPW) {
-        const int q = p - C::NPX;
-        L.gi = q / (4 * CT);
-        L.base = wscales + (int64_t)min(32 * CT * cb + 8 * (q % (4 * CT)), geo.n_pad - 8) * 2;
-        L.stride = (uint32_t)geo.n_pad * 2;
-      } else {
-        const int q = p - C::NPX - C::NPW;
-        L.gi = q / (4 * (RT > 0 ? RT : 1));
-        L.base = l1scales + (int64_t)(8 * (q % (4 * (RT > 0 ? RT : 1)))) * 2;
-        L.stride = (uint32_t)geo.r_pad32 * 2;
-      }
-    }
-    return L;
-  };
-  const Shared sl0 = shared_load(wave % C::NSH);
-  const Shared sl1 = shared_load((wave + MW) % C::NSH);   // issued in fp8 mode only
-
-  // ---- roles ----
+  // ---- roles: wavefront w < RT column w of the H tiles; residual wavefront
+  // ri column tile ri % CT, part ri / CT of every chunk ----
   const bool hw = wave < RT;
-  const int ri = hw ? -1 : res_index(RT, wave);
-  const int nf = hw ? MCG : (ri < C::NITEM ? (C::NITEM - ri + C::NRW - 1) / C::NRW : 0);
+  const int ri = hw ? 0 : res_index(RT, wave);
+  const int jt = ri % CT, ph = hw ? 0 : ri / CT;
+  const bool rbusy = !hw && ph < C::NPH;
+  const int ct = min(cb * CT + jt, ct32 - 1);   // column tile (past the last: never stored)
+  const int stile = hw ? TB + wave : TB + RT + jt;   // this wavefront's column of scales
+  const auto bbuf = m_buffer(hw ? a.packed + geo.off_l1 + (int64_t)wave * KG * 1024
+                                : a.packed + geo.off_w + (int64_t)ct * KG * 1024, (uint32_t)KG * 1024u);
+  const uint32_t lane16 = lane * 16;
 
-  // stage-2 operands, loaded first: wavefront j < CT the L2 blocks of tile j,
-  // the last wavefront the L2 scales of all CT tiles
-  auto stage2_loads = [&]() {
-    if constexpr (RT > 0) {
-      if (wave < CT) {
-        const int ct = min(cb * CT + wave, ct32 - 1);
+  // ---- staging: wavefront w the activation blocks w + 8 q of every chunk (TB
+  // tiles), thread t the 16-byte scale pieces t + 512 q: 8 consecutive rows of
+  // one group, written to LDS with a row's groups together ----
+  constexpr int XB = FP8 ? 2048 : 1024, XR = FP8 ? 2 : 1;
+  __amdgpu_buffer_rsrc_t abuf[TB];
 #pragma unroll
-        for (int rb = 0; rb < C::RB; rb++)
-          mdma(l2codes + (((int64_t)ct * C::RB + rb) * 64 + lane) * 16,
-               lds0 + C::OFF_L2 + (wave * C::RB + rb) * 1024);
-      }
-      if (wave == MW - 1) {
-        const int q0 = lane, q = q0 < C::RB * CT * 4 ? q0 : 0;
-        const int h = q / (4 * CT), j = (q / 4) % CT, part = q % 4;
-        const int col = min(32 * (cb * CT + j) + 8 * part, geo.n_pad - 8);
-        const int hg = h * 64 / geo.gr;   // rank group of 64-rank block h (gr >= 64 here)
-        mdma(l2scales + ((int64_t)hg * geo.n_pad + col) * 2, lds0 + C::OFF_L2 + CT * C::RB * 1024);
-      }
+  for (int t = 0; t < TB; t++)
+    abuf[t] = m_buffer(reinterpret_cast<const uint8_t *>(a.xc) +
+                       (int64_t)min(tb * TB + t, ms / 32 - 1) * KG * XB, (uint32_t)KG * XB);
+  // (threads past the last piece repeat one: same bytes, same place)
+  const uint8_t *sbase[C::SPT];
+  uint32_t sstride[C::SPT], spiece[C::SPT];
+#pragma unroll
+  for (int q = 0; q < C::SPT; q++) {
+    const int p0 = tid + 64 * MW * q, p = p0 < C::NP ? p0 : p0 % C::NP;
+    spiece[q] = p;
+    const int tile = p / (4 * C::CI), part = p % 4;
+    if (tile < TB) {
+      sbase[q] = reinterpret_cast<const uint8_t *>(a.xs) +
+                 (int64_t)(32 * min(tb * TB + tile, ms / 32 - 1) + 8 * part) * 2;
+      sstride[q] = (uint32_t)ms * 2;
+    } else if (tile < TB + RT) {
+      sbase[q] = a.packed + geo.off_l1s + (32 * (tile - TB) + 8 * part) * 2;
+      sstride[q] = (uint32_t)geo.r_pad32 * 2;
+    } else {
+      sbase[q] = a.packed + geo.off_ws +
+                 (int64_t)(32 * min(cb * CT + tile - TB - RT, ct32 - 1) + 8 * part) * 2;
+      sstride[q] = (uint32_t)geo.n_pad * 2;
     }
-  };
-
-  // expand chunk c's raw activation codes into fp8 operand bytes: the two
-  // residual wavefronts with the fewest items, MCG / 2 groups each, one lane
-  // per 16-byte lane slot
-  const int ex = ri >= C::NRW - 2 ? ri - (C::NRW - 2) : -1;   // expansion wavefront (or none)
-  auto expand = [&](int c, uint32_t slot_off) {
-    if (!FP8 && ex >= 0) {
-#pragma unroll
-      for (int q = 0; q < MCG / 2; q++) {
-        const int gi = ex * (MCG / 2) + q;
-        const u32x4 raw = *reinterpret_cast<const u32x4 *>(smem + slot_off + C::S_X +
-                                                           gi * 1024 + lane * 16);
-        const v8i u = unpack32(raw);
-        uint8_t *E = smem + C::OFF_XE + (c & 1) * C::XEB + gi * 2048 + lane * 32;
-        *reinterpret_cast<u32x4 *>(E) = u32x4{(uint32_t)u[0], (uint32_t)u[1], (uint32_t)u[2], (uint32_t)u[3]};
-        *reinterpret_cast<u32x4 *>(E + 16) = u32x4{(uint32_t)u[4], (uint32_t)u[5], (uint32_t)u[6], (uint32_t)u[7]};
-      }
-    }
-  };
-
-  // The K loop of one role with its per-chunk load count as a constant:
-  // H wavefronts walk their tile over the MCG groups of every chunk, residual
-  // wavefronts their NF items e = ri + NRW k (group e / CT, tile e % CT).
-  auto k_loop = [&](auto HC, auto NFC, auto &acc) {
-    constexpr bool H = decltype(HC)::value;
-    constexpr int NF = decltype(NFC)::value;
-    constexpr int PER = C::SHL + NF;   // loads per chunk
-    auto item_gi = [&](int k) { return H ? k : (ri + C::NRW * k) / CT; };
-    auto item_tile = [&](int k) { return (ri + C::NRW * k) % CT; };
-    auto item_frag = [&](int k) { return H ? wave * MCG + k : RT * MCG + ri + C::NRW * k; };
-    // Loads of one chunk.  Full chunks advance two streams: the shared load
-    // (a per-lane address and per-lane chunk stride) and this wavefront's
-    // block loads (wave-uniform bases in scalar registers, lane offset
-    // 16 * lane, MCG KiB per chunk).  A chunk that runs past the last K-group
-    // clamps its groups to the last one.
-    const uint8_t *sh_addr = sl0.base + (uint64_t)(sl0.gi >> sl0.shift) * sl0.stride;
-    const uint64_t sh_inc = (uint64_t)(MCG >> sl0.shift) * sl0.stride;
-    const uint8_t *sh_addr1 = sl1.base + (uint64_t)(sl1.gi >> sl1.shift) * sl1.stride;
-    const uint64_t sh_inc1 = (uint64_t)(MCG >> sl1.shift) * sl1.stride;
-    const uint32_t lane16 = lane * 16;
-    const uint8_t *fb[NF > 0 ? NF : 1];
-#pragma unroll
-    for (int k = 0; k < NF; k++)
-      fb[k] = m_uniform(H ? l1codes + ((int64_t)wave * KG + item_gi(k)) * 1024
-                          : wcodes + ((int64_t)min(cb * CT + item_tile(k), ct32 - 1) * KG + item_gi(k)) * 1024);
-    uint32_t islot = 0;   // ring offset of the next chunk to issue
-    // (full: the chunk is known to lie within K)
-    auto issue = [&](int c, auto full) {
-      const uint32_t slot = lds0 + islot;
-      if (decltype(full)::value || MCG * (c + 1) <= KG) {
-        mdma(sh_addr, slot + sl0.dst);
-        if constexpr (FP8) mdma(sh_addr1, slot + sl1.dst);
-#pragma unroll
-        for (int k = 0; k < NF; k++) {
-          mdma_s(lane16, fb[k], slot + C::S_FR + item_frag(k) * 1024);
-          fb[k] += MCG * 1024;
-        }
-      } else {
-        mdma(sl0.base + (uint64_t)(min(MCG * c + sl0.gi, KG - 1) >> sl0.shift) * sl0.stride, slot + sl0.dst);
-        if constexpr (FP8)
-          mdma(sl1.base + (uint64_t)(min(MCG * c + sl1.gi, KG - 1) >> sl1.shift) * sl1.stride, slot + sl1.dst);
-#pragma unroll
-        for (int k = 0; k < NF; k++) {
-          const int g = min(MCG * c + item_gi(k), KG - 1);
-          mdma_s(lane16, m_uniform(fb[k] - (MCG * c + item_gi(k) - g) * 1024),
-                 slot + C::S_FR + item_frag(k) * 1024);
-          fb[k] += MCG * 1024;
-        }
-      }
-      sh_addr += sh_inc;
-      sh_addr1 += sh_inc1;
-      islot = islot + C::SLOT == D * C::SLOT ? 0 : islot + C::SLOT;
-    };
-
-    mwait_vm<0>();
-    stage2_loads();
-    for (int s = 0; s < D - 1; s++)
-      if (s < NCH) issue(s, std::false_type{});
-    if (D - 1 <= NCH) mwait_vm<(D - 2) * PER>();   // chunk 0 has landed
-    else mwait_vm<0>();
-    __syncthreads();
-    expand(0, 0);
-    uint32_t rslot = 0;   // ring offset of chunk c
-    // One chunk.  steady: chunk c + D - 1 is issued and lies within K (so
-    // chunks c and c + 1 do too): no test of the chunk index, and so no
-    // branch in the chunk (the chunks before the last D are all such).
-    auto chunk = [&](int c, auto steady_c) {
-      constexpr bool steady = decltype(steady_c)::value;
-      // chunk c + 1 has landed for its expansion (fp8: chunk c, read as
-      // loaded); near the end of K nothing is issued past the last chunk, so
-      // everything issued is waited for
-      if (steady || c + D - 1 <= NCH) mwait_vm<(FP8 ? D - 2 : D - 3) * PER>();
-      else mwait_vm<0>();
-      __syncthreads();             // chunk c's operands are visible; chunk c - 1 is consumed
-      if (steady || c + D - 1 < NCH) issue(c + D - 1, steady_c);   // into chunk c - 1's slot
-      if (steady || c + 1 < NCH) expand(c + 1, rslot + C::SLOT == D * C::SLOT ? 0 : rslot + C::SLOT);
-      if constexpr (NF > 0) {
-        const uint8_t *S = smem + rslot;
-        const uint8_t *XE = smem + C::OFF_XE + (c & 1) * C::XEB;
-        v8i av[NF];
-        u32x4 bv[NF];
-        uint32_t sa[NF], sb[NF];
-#pragma unroll
-        for (int k = 0; k < NF; k++) {
-          const int gi = item_gi(k);
-          if constexpr (FP8) {
-            const u32x4 lo = *reinterpret_cast<const u32x4 *>(S + C::S_X + gi * 2048 + lane * 16);
-            const u32x4 hi = *reinterpret_cast<const u32x4 *>(S + C::S_X + gi * 2048 + 1024 + lane * 16);
-            av[k] = v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-          } else {
-            av[k] = lds_v8i(XE + gi * 2048 + lane * 32);
-          }
-          bv[k] = *reinterpret_cast<const u32x4 *>(S + C::S_FR + item_frag(k) * 1024 + lane * 16);
-          const uint32_t s_a = *reinterpret_cast<const uint16_t *>(S + C::S_SC + (gi * 32 + l32) * 2);
-          sa[k] = steady || MCG * c + gi < KG ? s_a : 0u;   // a group past K adds exactly zero
-          const int so = H ? (C::NPX + C::NPW) * 16 + (gi * 32 * RT + 32 * wave + l32) * 2
-                           : C::NPX * 16 + (gi * 32 * CT + 32 * item_tile(k) + l32) * 2;
-          sb[k] = *reinterpret_cast<const uint16_t *>(S + C::S_SC + so);
-        }
-        if (H && gk == 2) {
-          // 128-wide groups: the half sums of a group's two blocks add
-          // exactly in the matrix core, then one fma per element and group
-          // (the oracle's step)
-#pragma unroll
-          for (int kp = 0; kp < NF / 2; kp++) {
-            const v16f c0 = m_codes_half(av[2 * kp], unpack32(bv[2 * kp]));
-            const v16f cg = m_codes_half_acc(av[2 * kp + 1], unpack32(bv[2 * kp + 1]), c0);
-            const v16f pg = m_outer2(sa[2 * kp], sb[2 * kp]);
-#pragma unroll
-            for (int v = 0; v < 16; v++) acc[0][v] = fmaf(cg[v], pg[v], acc[0][v]);
-          }
-          rslot = rslot + C::SLOT == D * C::SLOT ? 0 : rslot + C::SLOT;
-          return;
-        }
-        // Every operand of the chunk is read before the first product; then
-        // item k's two products go to the matrix core while the vector ALU
-        // expands item k + 1's weight codes and applies item k - 1's fmas.
-        __builtin_amdgcn_sched_barrier(0);
-        v8i bu = unpack32(bv[0]);
-        v16f cp = m_codes_half(av[0], bu);
-        v16f pp = m_outer2(sa[0], sb[0]);
-        if constexpr (NF > 1) bu = unpack32(bv[1]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int k = 1; k <= NF; k++) {
-          v16f cn, pn;
-          if (k < NF) {
-            cn = m_codes_half(av[k], bu);
-            pn = m_outer2(sa[k], sb[k]);
-            if (k + 1 < NF) bu = unpack32(bv[k + 1]);
-          }
-          v16f &t = acc[H ? 0 : k - 1];
-#pragma unroll
-          for (int v = 0; v < 16; v++) t[v] = fmaf(cp[v], pp[v], t[v]);
-          if (k < NF) {
-            // one product, the next operand's expansion, the other product,
-            // the fmas
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (k + 1 < NF) __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            cp = cn;
-            pp = pn;
-          }
-        }
-      }
-      rslot = rslot + C::SLOT == D * C::SLOT ? 0 : rslot + C::SLOT;
-    };
-    int c = 0;
-    for (; MCG * (c + D) <= KG; c++) chunk(c, std::true_type{});
-    for (; c < NCH; c++) chunk(c, std::false_type{});
-  };
-
-  constexpr int NACC = C::NF_MAX > 1 ? C::NF_MAX : 1;
-  v16f acc[NACC];
-#pragma unroll
-  for (int k = 0; k < NACC; k++) acc[k] = v16f{0};
-  if (hw) {
-    if constexpr (RT > 0) k_loop(std::true_type{}, std::integral_constant<int, MCG>{}, acc);
-  } else if (nf == 4) {
-    if constexpr (C::NF_MAX >= 4) k_loop(std::false_type{}, std::integral_constant<int, 4>{}, acc);
-  } else if (nf == 3) {
-    if constexpr (C::NF_MAX >= 3) k_loop(std::false_type{}, std::integral_constant<int, 3>{}, acc);
-  } else if (nf == 2) {
-    if constexpr (C::NF_MAX >= 2) k_loop(std::false_type{}, std::integral_constant<int, 2>{}, acc);
-  } else if (nf == 1) {
-    k_loop(std::false_type{}, std::integral_constant<int, 1>{}, acc);
-  } else {
-    k_loop(std::false_type{}, std::integral_constant<int, 0>{}, acc);
   }
-  __syncthreads();   // every wavefront is done with the ring
+  u32x4 areg[C::APW][TB][XR], sreg[C::SPT];
+  auto stage_load = [&](int c) {   // blocks past K read zeros, scale rows past it the last row
+#pragma unroll
+    for (int w = 0; w < C::APW; w++) {
+      const uint32_t off = (uint32_t)(c * MCG + w * MW + wave) * XB + lane16;
+#pragma unroll
+      for (int t = 0; t < TB; t++)
+#pragma unroll
+        for (int x = 0; x < XR; x++) areg[w][t][x] = m_load16(abuf[t], off + x * 1024);
+    }
+#pragma unroll
+    for (int q = 0; q < C::SPT; q++) {
+      const uint32_t row = min((uint32_t)(c * C::CI) + spiece[q] / 4 % C::CI, (uint32_t)(KQ - 1));
+      sreg[q] = *(const __attribute__((address_space(1))) u32x4 *)(sbase[q] + (uint64_t)row * sstride[q]);
+    }
+  };
+  auto stage_write = [&](int c) {
+    uint8_t *B = smem + (c & 1) * C::BUF;
+#pragma unroll
+    for (int w = 0; w < C::APW; w++) {
+#pragma unroll
+      for (int t = 0; t < TB; t++) {
+        u32x4 lo, hi;
+        if constexpr (FP8) {
+          lo = areg[w][t][0];
+          hi = areg[w][t][1];
+        } else {
+          const v8i u = unpack32(areg[w][t][0]);
+          lo = u32x4{(uint32_t)u[0], (uint32_t)u[1], (uint32_t)u[2], (uint32_t)u[3]};
+          hi = u32x4{(uint32_t)u[4], (uint32_t)u[5], (uint32_t)u[6], (uint32_t)u[7]};
+        }
+        uint8_t *A = B + (t * MCG + w * MW + wave) * 2048 + lane16;
+        *reinterpret_cast<u32x4 *>(A) = lo;
+        *reinterpret_cast<u32x4 *>(A + 1024) = hi;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < C::SPT; q++) {
+      const uint32_t p = spiece[q];
+      uint16_t *S = reinterpret_cast<uint16_t *>(B + C::S_S) + (p / (4 * C::CI) * 32 + p % 4 * 8) * C::CI + p / 4 % C::CI;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        S[2 * e * C::CI] = (uint16_t)(sreg[q][e] & 0xffffu);
+        S[(2 * e + 1) * C::CI] = (uint16_t)(sreg[q][e] >> 16);
+      }
+    }
+  };
 
-  // ---- H tiles and residual partials -> LDS ----
+  v16f acc[TB];
+#pragma unroll
+  for (int t = 0; t < TB; t++) acc[t] = v16f{0};
+
+  // The K loop of one role: IP groups of every chunk (from group ph IP on),
+  // with the blocks of PC chunks in flight.
+  auto k_loop = [&](auto IPCC, auto PCC) {
+    constexpr int IP = decltype(IPCC)::value, PC = decltype(PCC)::value, D = IP * PC;
+    u32x4 ring[D][GK];
+    uint32_t boff = (uint32_t)(ph * IP * GK) * 1024u + lane16;
+    auto load = [&](int s, uint32_t off) {   // slot s: group s % IP of this wavefront's part of a chunk
+#pragma unroll
+      for (int u = 0; u < GK; u++) ring[s][u] = m_load16(bbuf, off + (s % IP * GK + u) * 1024);
+    };
+    stage_load(0);
+#pragma unroll
+    for (int s = 0; s < D; s++) load(s, boff + s / IP * (MCG * 1024));
+    boff += PC * MCG * 1024;
+    stage_write(0);
+    stage_load(1);
+    m_barrier();
+    // products waiting for their fmas: those of the tile before, so that the
+    // matrix core works on one tile while the vector ALU rescales another
+    v16f pc = v16f{0}, pp = v16f{0};
+    v8i bu[GK];
+#pragma unroll
+    for (int b = 0; b < GK; b++) bu[b] = unpack32(ring[0][b]);
+    for (int c0 = 0; c0 < NCH; c0 += PC) {
+#pragma unroll
+      for (int u = 0; u < PC; u++) {
+        const int c = c0 + u;
+        if (PC == 1 || c < NCH) {
+        const uint8_t *A = smem + (c & 1) * C::BUF + ph * IP * GK * 2048 + lane16;
+        const uint8_t *S = smem + (c & 1) * C::BUF + C::S_S + (l32 * C::CI + ph * IP) * 2;
+        v8i av[2][TB][GK];
+        auto read_a = [&](int i) {
+#pragma unroll
+          for (int t = 0; t < TB; t++)
+#pragma unroll
+            for (int b = 0; b < GK; b++) {
+              const uint8_t *p = A + (t * MCG + i * GK + b) * 2048;
+              av[i & 1][t][b] = m_join(*reinterpret_cast<const u32x4 *>(p), *reinterpret_cast<const u32x4 *>(p + 1024));
+            }
+        };
+        u32x2 sa[TB][IP / 4], sb[IP / 4];
+        read_a(0);
+#pragma unroll
+        for (int q = 0; q < IP / 4; q++) {
+#pragma unroll
+          for (int t = 0; t < TB; t++)
+            sa[t][q] = *reinterpret_cast<const u32x2 *>(S + (t * 32 * C::CI + 4 * q) * 2);
+          sb[q] = *reinterpret_cast<const u32x2 *>(S + (stile * 32 * C::CI + 4 * q) * 2);
+        }
+#pragma unroll
+        for (int i = 0; i < IP; i++) {
+          const int s = u * IP + i;
+#pragma unroll
+          for (int t = 0; t < TB; t++) {
+            // the short scale product first: the code product behind it waits
+            // half as long for the matrix core as in the other order
+            const v16f cp = m_outer2(sa[t][i / 4], sb[i / 4], i);
+            __builtin_amdgcn_sched_barrier(0);
+            v16f cc = m_codes_half(av[i & 1][t][0], bu[0]);
+            if constexpr (GK == 2) cc = m_codes_half_acc(av[i & 1][t][1], bu[1], cc);
+            __builtin_amdgcn_sched_barrier(0);
+            if (t == 0) {
+              load(s, boff);
+              if (i + 1 < IP) read_a(i + 1);
+              if (i == 1) stage_write(c + 1);
+              if (i == 2) stage_load(c + 2);
+            }
+            v16f &d = acc[(t + TB - 1) % TB];
+#pragma unroll
+            for (int v = 0; v < 16; v++) d[v] = fmaf(pc[v], pp[v], d[v]);
+            if (t == TB - 1) {
+#pragma unroll
+              for (int b = 0; b < GK; b++) bu[b] = unpack32(ring[(s + 1) % D][b]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            pc = cc;
+            pp = cp;
+          }
+        }
+        boff += MCG * 1024;
+        m_barrier();
+        }
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[TB - 1][v] = fmaf(pc[v], pp[v], acc[TB - 1][v]);
+  };
+  // a wavefront without tiles: staging and barriers only
+  auto k_idle = [&]() {
+    stage_load(0);
+    stage_write(0);
+    stage_load(1);
+    m_barrier();
+    for (int c = 0; c < NCH; c++) {
+      stage_write(c + 1);
+      stage_load(c + 2);
+      m_barrier();
+    }
+  };
+
+  // stage-2 operands of this wavefront's column tile, loaded ahead of the K loop
+  u32x4 l2raw[C::RB > 0 ? C::RB : 1];
+  uint32_t l2s[C::RB > 0 ? C::RB : 1];
+  if constexpr (RT > 0) {
+    const uint16_t *l2scales = reinterpret_cast<const uint16_t *>(a.packed + geo.off_l2s);
+#pragma unroll
+    for (int rb = 0; rb < C::RB; rb++) {
+      const int hg = rb * 64 / geo.gr;   // rank group of 64-rank block rb
+      l2raw[rb] = *reinterpret_cast<const u32x4 *>(a.packed + geo.off_l2 + ((int64_t)ct * C::RB + rb) * 1024 + lane16);
+      l2s[rb] = l2scales[(int64_t)hg * geo.n_pad + 32 * ct + l32];
+    }
+  }
+
+  if (C::IPC == C::CI && (hw || rbusy)) {
+    k_loop(std::integral_constant<int, C::CI>{}, std::integral_constant<int, 1>{});
+  } else if (hw) {
+    if constexpr (RT > 0) k_loop(std::integral_constant<int, C::CI>{}, std::integral_constant<int, 1>{});
+  } else if (rbusy) {
+    k_loop(std::integral_constant<int, C::IPC>{}, std::integral_constant<int, C::IPC == 4 && GK == 1 ? 2 : 1>{});
+  } else {
+    k_idle();
+  }
+
+  // ---- H tiles and residual partials -> LDS (after the last barrier every
+  // wavefront is done with the chunk buffers) ----
   float *HS = reinterpret_cast<float *>(smem + C::E_HS);
   uint8_t *QS = smem + C::E_QS;
   float *SHS = reinterpret_cast<float *>(smem + C::E_SH);
   float *RES = reinterpret_cast<float *>(smem + C::E_RES);
   if (hw) {
 #pragma unroll
-    for (int v = 0; v < 16; v++) HS[row_of_32x32(lane, v) * C::HSTR + 32 * wave + l32] = acc[0][v];
-  } else {
+    for (int t = 0; t < TB; t++)
 #pragma unroll
-    for (int k = 0; k < NACC; k++) {
-      if (k < nf) {
-        const int e = ri + C::NRW * k;
+      for (int v = 0; v < 16; v++)
+        HS[(32 * t + row_of_32x32(lane, v)) * C::HSTR + 32 * wave + l32] = acc[t][v];
+  } else if (C::NPH > 1 && rbusy && ph > 0) {
+    float *P = RES + (jt * (C::NPH - 1) + ph - 1) * TB * 1024 + lane * 4;
 #pragma unroll
-        for (int v = 0; v < 16; v += 4)
-          *reinterpret_cast<v4f *>(RES + (e * 64 + lane) * 16 + v) =
-              v4f{acc[k][v], acc[k][v + 1], acc[k][v + 2], acc[k][v + 3]};
-      }
-    }
+    for (int t = 0; t < TB; t++)
+#pragma unroll
+      for (int v = 0; v < 16; v += 4)
+        *reinterpret_cast<v4f *>(P + t * 1024 + v * 64) = v4f{acc[t][v], acc[t][v + 1], acc[t][v + 2], acc[t][v + 3]};
   }
   if constexpr (RT > 0) {
     const int r = geo.r;
     if (r < C::RB * 64)
-      for (int idx = tid; idx < 32 * C::RB * 64; idx += 64 * MW) {
+      for (int idx = tid; idx < C::ROWS * C::RB * 64; idx += 64 * MW) {
         const int row = idx / (C::RB * 64), j = idx % (C::RB * 64);
         if (j >= r) QS[row * C::QSTR + j] = 0;
       }
   }
-  __syncthreads();
+  m_barrier();
 
   // ---- re-quantize H per token and rank group (s_H stays fp32) ----
   if constexpr (RT > 0) {
     const int r = geo.r, gr = geo.gr, rg = r / gr;
-    const int subs = gr / 8;                // lanes per (token, rank group): 1, 2, 4 or 8
-    const int work = 32 * rg * subs;        // <= 512
+    const int subs = gr / 8;                // lanes per (token, rank group): 1, 2, 4, 8 or 16
+    const int work = C::ROWS * rg * subs;   // <= 512 TB
     const bool dbg = a.dbg_h != nullptr && cb == 0;
-    const bool valid = tid < work;
-    const int pair = tid / subs, sub = tid % subs;
-    const int row = pair / rg, hg = pair % rg;
-    const int j0 = hg * gr + sub * 8;
-    const int grow = 32 * tb + row;
-    float hv[8];
-    float amax = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 8; e++) {
-      hv[e] = valid ? HS[row * C::HSTR + j0 + e] : 0.0f;
-      amax = fmaxf(amax, fabsf(hv[e]));
-    }
-    for (int msk = 1; msk < subs; msk <<= 1) amax = fmaxf(amax, __shfl_xor(amax, msk));
-    const float shv = amax / 7.0f;   // IEEE division
-    if (valid) {
-      uint32_t w0 = 0, w1 = 0;
+    for (int base = 0; base < 64 * MW * TB; base += 64 * MW) {
+      const int idx = base + tid;
+      const bool valid = idx < work;
+      const int pair = idx / subs, sub = idx % subs;
+      const int row = pair / rg, hg = pair % rg;
+      const int j0 = hg * gr + sub * 8;
+      const int grow = C::ROWS * tb + row;
+      float hv[8];
+      float amax = 0.0f;
 #pragma unroll
       for (int e = 0; e < 8; e++) {
-        int qv = 0;
-        if (shv != 0.0f) {
-          float tq = __builtin_rintf(hv[e] / shv);
-          tq = tq > 7.0f ? 7.0f : (tq < -7.0f ? -7.0f : tq);
-          qv = (int)tq;
-        }
-        const uint32_t bq = code_to_fp8(qv);
-        if (e < 4) w0 |= bq << (8 * e); else w1 |= bq << (8 * (e - 4));
-        if (dbg && grow < m) {
-          a.dbg_h[(int64_t)grow * r + j0 + e] = hv[e];
-          a.dbg_qh[(int64_t)grow * r + j0 + e] = (int8_t)qv;
-        }
+        hv[e] = valid ? HS[row * C::HSTR + j0 + e] : 0.0f;
+        amax = fmaxf(amax, fabsf(hv[e]));
       }
-      *reinterpret_cast<uint32_t *>(QS + row * C::QSTR + j0) = w0;
-      *reinterpret_cast<uint32_t *>(QS + row * C::QSTR + j0 + 4) = w1;
-      if (sub == 0) {
-        SHS[hg * 32 + row] = shv;
-        if (dbg && grow < m) a.dbg_sh[(int64_t)grow * rg + hg] = shv;
+      for (int msk = 1; msk < subs; msk <<= 1) amax = fmaxf(amax, __shfl_xor(amax, msk));
+      const float shv = amax / 7.0f;   // IEEE division
+      if (valid) {
+        uint32_t w0 = 0, w1 = 0;
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+          int qv = 0;
+          if (shv != 0.0f) {
+            float tq = __builtin_rintf(hv[e] / shv);
+            tq = tq > 7.0f ? 7.0f : (tq < -7.0f ? -7.0f : tq);
+            qv = (int)tq;
+          }
+          const uint32_t bq = code_to_fp8(qv);
+          if (e < 4) w0 |= bq << (8 * e); else w1 |= bq << (8 * (e - 4));
+          if (dbg && grow < m) {
+            a.dbg_h[(int64_t)grow * r + j0 + e] = hv[e];
+            a.dbg_qh[(int64_t)grow * r + j0 + e] = (int8_t)qv;
+          }
+        }
+        *reinterpret_cast<uint32_t *>(QS + row * C::QSTR + j0) = w0;
+        *reinterpret_cast<uint32_t *>(QS + row * C::QSTR + j0 + 4) = w1;
+        if (sub == 0) {
+          SHS[hg * C::ROWS + row] = shv;
+          if (dbg && grow < m) a.dbg_sh[(int64_t)grow * rg + hg] = shv;
+        }
       }
     }
-    __syncthreads();
+    m_barrier();
   }
 
-  // ---- stage 2 and the single epilogue: wavefront j < CT stores tile j ----
-  if (wave < CT) {
-    const int j = wave;
-    const int ct = cb * CT + j;
-    if (ct < ct32) {
+  // ---- stage 2 and the single epilogue: the first wavefront of each column ----
+  if (!hw && ph == 0 && cb * CT + jt < ct32) {
+#pragma unroll
+    for (int t = 0; t < TB; t++) {
       v16f ylr = v16f{0};
       if constexpr (RT > 0) {
-        const uint8_t *L2S = smem + C::OFF_L2;
+        // one fma per rank group (the oracle's step): a 128-rank group (r = 128
+        // in 128-wide groups) first adds its two 64-rank blocks' exact sums
+        constexpr int BPG = RT == 4 && GK == 2 ? 2 : 1;   // 64-rank blocks per rank group
 #pragma unroll
-        for (int rb = 0; rb < C::RB; rb++) {
-          const v8i qa = lds_v8i(QS + l32 * C::QSTR + rb * 64 + (lane >> 5) * 32);
-          const v8i lb = unpack32(*reinterpret_cast<const u32x4 *>(L2S + (j * C::RB + rb) * 1024 + lane * 16));
-          const float sl2 = half_bits_to_float(*reinterpret_cast<const uint16_t *>(
-              L2S + CT * C::RB * 1024 + ((rb * CT + j) * 32 + l32) * 2));
-          const v16f cbv = mfma_codes_32x32x64(qa, lb);
+        for (int hg = 0; hg < C::RB / BPG; hg++) {
+          v16f cbv = v16f{0};
+#pragma unroll
+          for (int q = 0; q < BPG; q++) {
+            const int rb = hg * BPG + q;
+            const uint8_t *qrow = QS + (32 * t + l32) * C::QSTR + rb * 64 + (lane >> 5) * 32;
+            const v8i qa = m_join(*reinterpret_cast<const u32x4 *>(qrow), *reinterpret_cast<const u32x4 *>(qrow + 16));
+            const v8i lb = unpack32(l2raw[rb]);
+            cbv = q == 0 ? mfma_codes_32x32x64(qa, lb) : mfma_codes_32x32x64_acc(qa, lb, cbv);
+          }
+          const float sl2 = half_bits_to_float((uint16_t)l2s[hg * BPG]);
 #pragma unroll
           for (int v = 0; v < 16; v++)
-            ylr[v] = fmaf(cbv[v], SHS[(rb * 64 / geo.gr) * 32 + row_of_32x32(lane, v)] * sl2, ylr[v]);
+            ylr[v] = fmaf(cbv[v], SHS[hg * C::ROWS + 32 * t + row_of_32x32(lane, v)] * sl2, ylr[v]);
         }
       }
       // the matrix-core products above read operands from every lane: keep
       // them out of the per-lane store branch below
       asm volatile("" : "+v"(ylr));
-      v16f yres = v16f{0};
+      v16f yres = acc[t];
 #pragma unroll
-      for (int gi = 0; gi < MCG; gi++) {
-        const float *rp = RES + ((gi * CT + j) * 64 + lane) * 16;
+      for (int p = 0; p < C::NPH - 1; p++) {
+        const float *rp = RES + ((jt * (C::NPH - 1) + p) * TB + t) * 1024 + lane * 4;
 #pragma unroll
         for (int v = 0; v < 16; v += 4) {
-          const v4f r4 = *reinterpret_cast<const v4f *>(rp + v);
+          const v4f r4 = *reinterpret_cast<const v4f *>(rp + v * 64);
           yres[v] += r4[0]; yres[v + 1] += r4[1]; yres[v + 2] += r4[2]; yres[v + 3] += r4[3];
         }
       }
@@ -579,7 +523,7 @@ __global__ __launch_bounds__(64 * MW, 1) void dual_gemm_mid_kernel(GemmArgs a, i
       if (col < geo.n) {
 #pragma unroll
         for (int v = 0; v < 16; v++) {
-          const int row = 32 * tb + row_of_32x32(lane, v);
+          const int row = C::ROWS * tb + 32 * t + row_of_32x32(lane, v);
           if (row < m) {
             const float yv = yres[v] + ylr[v];
             const uint16_t bits = a.bf16_out ? float_to_bf16_bits(yv) : float_to_half_bits(yv);
@@ -591,12 +535,12 @@ __global__ __launch_bounds__(64 * MW, 1) void dual_gemm_mid_kernel(GemmArgs a, i
   }
 }
 
-template <int RT, int CT, bool FP8>
+template <int TB, int RT, int CT, int GK, bool FP8>
 hipError_t launch_mid(const GemmArgs &a, hipStream_t s) {
-  using C = MCfg<RT, CT, FP8>;
-  const int n_rb = a.ms / 32;
+  using C = MCfg<TB, RT, CT, GK>;
+  const int n_rb = (a.ms / 32 + TB - 1) / TB;
   const int n_cb = (a.geo.n_pad / 32 + CT - 1) / CT;
-  auto kern = dual_gemm_mid_kernel<RT, CT, FP8>;
+  auto kern = dual_gemm_mid_kernel<TB, RT, CT, GK, FP8>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
   if (e != hipSuccess) return e;
@@ -604,59 +548,72 @@ hipError_t launch_mid(const GemmArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int CT, bool FP8>
-hipError_t launch_mid_rt(const GemmArgs &a, hipStream_t s) {
+template <int RT, int GK, bool FP8>
+hipError_t launch_mid_tiles(int tb, int ct, const GemmArgs &a, hipStream_t s) {
+  if (tb == 2) return launch_mid<2, RT, MW - RT, GK, FP8>(a, s);
+  if (ct == 1) return launch_mid<1, RT, 1, GK, FP8>(a, s);
+  return ct == 4 ? launch_mid<1, RT, 4, GK, FP8>(a, s) : launch_mid<1, RT, 2, GK, FP8>(a, s);
+}
+
+template <int GK, bool FP8>
+hipError_t launch_mid_rt(int tb, int ct, const GemmArgs &a, hipStream_t s) {
   switch (a.geo.r_pad32 / 32) {
-    case 0: return launch_mid<0, CT, FP8>(a, s);
-    case 1: return launch_mid<1, CT, FP8>(a, s);
-    case 2: return launch_mid<2, CT, FP8>(a, s);
-    case 4: return launch_mid<4, CT, FP8>(a, s);
+    case 0: return launch_mid_tiles<0, GK, FP8>(tb, ct, a, s);
+    case 1: return launch_mid_tiles<1, GK, FP8>(tb, ct, a, s);
+    case 2: return launch_mid_tiles<2, GK, FP8>(tb, ct, a, s);
+    case 4: return launch_mid_tiles<4, GK, FP8>(tb, ct, a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-template <bool FP8>
-hipError_t launch_mid_ct(int ct, const GemmArgs &a, hipStream_t s) {
-  if (ct == 1) return launch_mid_rt<1, FP8>(a, s);
-  return ct == 4 ? launch_mid_rt<4, FP8>(a, s) : launch_mid_rt<2, FP8>(a, s);
+
+// Tile choices.  A workgroup runs one serial K loop, so a launch takes the
+// rounds of workgroups over the 256 CUs times a round's time: a part that does
+// not depend on K (filling the pipeline, H's re-quantization, stage 2) and a
+// time per 64-wide K block.  Measured on one round at K = 2048 and 8192 (ns
+// per block, 64-wide groups, ranks 0 / up to 64 / 128): 32 tokens x 1 or 2
+// column tiles 70 / 112 / 130 (the H wavefront's own chain; r = 0: the column
+// tiles), x 4 tiles 107 / 156 / 190; 64 tokens x all eight columns of tiles
+// 320 at every rank (four tile-groups per SIMD).  128-wide groups take 0.85
+// of that (one rescale per two blocks).
+struct MidPlan {
+  int tb, ct, ns;   // token tiles, column tiles (TB = 2: all columns that hold no H), time
+};
+
+MidPlan mid_cost(const GemmArgs &a, int tb, int ct) {
+  const int rt = a.geo.r_pad32 / 32, c = rt == 0 ? 0 : (rt <= 2 ? 1 : 2);
+  const int n_wg = (a.ms / 32 + tb - 1) / tb * ((a.geo.n_pad / 32 + ct - 1) / ct);
+  constexpr int kBlock[3][3] = {{70, 112, 130}, {107, 156, 190}, {320, 320, 310}};
+  int block = kBlock[tb == 2 ? 2 : (ct == 4 ? 1 : 0)][c];
+  if (a.geo.gk == 2) block = block * 85 / 100;
+  const int64_t round = (tb == 2 ? 6000 : 3500) + (int64_t)block * (a.geo.k / 64);
+  const int64_t ns = 3000 + (n_wg + 255) / 256 * round;
+  return MidPlan{tb, ct, ns < (1 << 30) ? (int)ns : 1 << 30};
 }
 
-// Each work-group runs one serial K loop whose length grows with the
-// tile-groups it owns (H and residual), so the cost of a choice of CT is the
-// number of rounds of work-groups over the 256 CUs times the tile-groups per
-// work-group and chunk.
-// Relative time of a launch with CT column tiles per work-group: rounds of
-// work-groups over the 256 CUs x (per-chunk tile-groups of a work-group plus
-// a fixed latency worth about three tile-groups per chunk, measured at
-// K = N = 4096: 9.5 / 14.5 / 18 us per round for r = 0 and CT = 1 / 2 / 4,
-// 16 / 18.5 / 22 us for r = 64).
-int mid_cost(int rt, int ct, int n_rb, int ct32) {
-  const int n_wg = n_rb * ((ct32 + ct - 1) / ct);
-  return (n_wg + 255) / 256 * (3 + rt + ct);
-}
-
-// the tile count of least cost (and that cost)
-int mid_tiles(const GemmArgs &a, int *cost) {
-  const int rt = a.geo.r_pad32 / 32, ct32 = a.geo.n_pad / 32, n_rb = a.ms / 32;
-  int ct = 1;
-  for (int c : {2, 4})
-    if (mid_cost(rt, c, n_rb, ct32) < mid_cost(rt, ct, n_rb, ct32)) ct = c;
-  if (a.mid_ct > 0) ct = a.mid_ct;   // forced by the test entry (1, 2 or 4, validated there)
-  if (cost) *cost = mid_cost(rt, ct, n_rb, ct32);
-  return ct;
+// the plan of least time; exact: only those whose wavefronts own their column
+// tiles alone, so that Y is summed in ascending group order
+MidPlan mid_plan(const GemmArgs &a, bool exact) {
+  const int rt = a.geo.r_pad32 / 32;
+  if (a.mid_ct > 0) return MidPlan{1, a.mid_ct, 0};   // forced by the test entry (1, 2 or 4, validated there)
+  MidPlan best = mid_cost(a, 2, MW - rt);
+  for (int ct : {1, 2, 4}) {
+    if (exact && (ct != 4 || rt == 0)) continue;
+    const MidPlan p = mid_cost(a, 1, ct);
+    if (p.ns < best.ns) best = p;
+  }
+  return best;
 }
 
 }  // namespace
 
-int dual_gemm_mid_cost(const GemmArgs &a) {
-  int cost = 0;
-  mid_tiles(a, &cost);
-  return cost;
-}
+int dual_gemm_mid_ns(const GemmArgs &a) { return mid_plan(a, true).ns; }
 
-hipError_t launch_dual_gemm_mid(const GemmArgs &a, hipStream_t s) {
-  const int ct = mid_tiles(a, nullptr);
-  return act_codes_fp8(a.m) ? launch_mid_ct<true>(ct, a, s) : launch_mid_ct<false>(ct, a, s);
+hipError_t launch_dual_gemm_mid(const GemmArgs &a, bool exact, hipStream_t s) {
+  const MidPlan p = mid_plan(a, exact);
+  if (a.geo.gk == 2)
+    return act_codes_fp8(a.m) ? launch_mid_rt<2, true>(p.tb, p.ct, a, s) : launch_mid_rt<2, false>(p.tb, p.ct, a, s);
+  return act_codes_fp8(a.m) ? launch_mid_rt<1, true>(p.tb, p.ct, a, s) : launch_mid_rt<1, false>(p.tb, p.ct, a, s);
 }
 
 }  // namespace tq

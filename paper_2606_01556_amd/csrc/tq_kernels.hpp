@@ -50,7 +50,7 @@ struct GemmArgs {
   float *dbg_sh;        // optional [m][r/gr]
   int8_t *dbg_qh;       // optional [m][r]
   int force_kernel;     // -1: chosen by choose_kernel; else a kKernel* value (tests)
-  int mid_ct;           // 0: chosen by the mid kernel's cost model; else 1, 2 or 4 (tests)
+  int mid_ct;           // 0: the mid kernel's plan of least time; else 1, 2 or 4 column tiles (tests)
 };
 
 // gk: 64-wide K blocks per quantization group (1 or 2)
@@ -75,10 +75,10 @@ bool decode_fits(int m, int k);
 // the kernel launch_dual_gemm runs (values of tq_kernel in the C header)
 constexpr int kKernelDecode = 0, kKernelMid = 1, kKernelLarge = 2, kKernelPrefill = 3;
 int choose_kernel(const GemmArgs &a);
-hipError_t launch_dual_gemm_mid(const GemmArgs &a, hipStream_t s);      // mid sizes
-// relative time of the mid kernel's launch: rounds of work-groups over the
-// CUs x tile-groups per work-group and chunk (+3 for its fixed latency)
-int dual_gemm_mid_cost(const GemmArgs &a);
+// mid sizes; exact: Y summed in ascending group order
+hipError_t launch_dual_gemm_mid(const GemmArgs &a, bool exact, hipStream_t s);
+// estimated time in ns of the mid kernel's best plan with that order
+int dual_gemm_mid_ns(const GemmArgs &a);
 hipError_t launch_dual_gemm_prefill(const GemmArgs &a, hipStream_t s);  // prefill sizes
 hipError_t launch_dual_gemm_large(const GemmArgs &a, hipStream_t s);    // large token counts
 // the layer without fusion (comparison baseline): residual GEMM, stage 1 to

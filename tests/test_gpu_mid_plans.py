@@ -1,0 +1,52 @@
+"""GPU parity of the mid kernel's plans: 64-token blocks (two token tiles per
+wavefront), and the plans that stand in for the large and prefill kernels,
+whose Y is bit-exact with the oracle."""
+import pytest
+
+import paper_2606_01556_amd as tq
+from test_gpu_parity import full_parity, say
+from tq_synth import random_codes_layer
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    tq.lib()
+    yield
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("M,K,N,r,group,bf16", [
+    (193, 576, 4768, 64, 64, False),    # odd token tiles (half a block past M), a chunk of one block
+    (130, 64, 13000, 64, 64, False),    # a single K-group
+    (200, 1152, 8000, 16, 128, True),   # 128-wide groups, half a chunk at the end of K
+    (161, 512, 10010, 0, 64, False),    # no H: all eight columns residual, ragged N
+    (350, 640, 5000, 128, 128, False),  # a 128-rank group in two blocks
+])
+def test_two_token_tiles(oracle_mod, M, K, N, r, group, bf16):
+    """Enough column tiles that 32-token blocks would take a second round over
+    the CUs, so the plan of least time has 64-token blocks; Y in the oracle's
+    order there, so bit-exact although the kernel is named "mid"."""
+    say(f"two token tiles M={M} K={K} N={N} r={r} group={group}")
+    d = random_codes_layer(M, K, N, r, seed=M + N + r)
+    g, o = full_parity(oracle_mod, d["X"], d["W_res"], d["L1"], d["L2"], bf16=bf16, group=group)
+    assert g["kernel"] == "mid"
+    assert (g["Ybits"] == (o["Ybf"] if bf16 else o["Y16"].view("uint16"))).all()
+
+
+@pytest.mark.parametrize("M,K,N,r,group,kernel", [
+    (577, 2048, 4070, 128, 128, "large"),    # 32-token blocks, four column tiles
+    (1025, 2496, 4100, 16, 64, "large"),     # 64-token blocks, odd token tiles, ragged N
+    (570, 4096, 14300, 128, 64, "prefill"),
+])
+def test_in_place_of_large_blocks(oracle_mod, M, K, N, r, group, kernel):
+    """Past 512 tokens (fp8 activation codes) where 128 x 256 blocks fill the
+    CUs badly: Y stays bit-exact (full_parity demands it under these names)."""
+    say(f"in place of {kernel} M={M} K={K} N={N} r={r} group={group}")
+    d = random_codes_layer(M, K, N, r, seed=M + N + r)
+    g, _ = full_parity(oracle_mod, d["X"], d["W_res"], d["L1"], d["L2"], group=group)
+    assert g["kernel"] == kernel
