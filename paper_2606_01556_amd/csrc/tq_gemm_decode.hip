@@ -5,37 +5,57 @@
 //
 // Work decomposition.  One work-group of sixteen wavefronts per CU owns CT
 // 16-column tiles of Y and streams their packed weights once.  H is small
-// (m x r) and every work-group forms all of it in its own registers, so no
-// work-group waits for another; the price is that each CU reads all of L1
-// (from L2, where the first reader leaves it) in addition to its columns.
-//  * Wavefront w < ceil(r / 16) owns rank tile w of H and walks every
-//    K-group pair in ascending order, so its fp32 chain (one fma per K-group,
-//    ascending, with the exact product I s_x) stays in registers and H is
-//    bit-identical to the oracle's.
-//  * The other wavefronts take the residual work: each owns one or two of
-//    the column tiles and every NPH-th K-group pair (NPH wavefronts share a
-//    tile group); their partial sums are added in a fixed order at the end
-//    (the order of Y's fp32 accumulation is free; H's is not).
-//  * Operands stream from global memory straight into registers through
-//    per-wavefront rings of 8 to 10 pairs (the L1 bytes come from L2, at its
-//    latency); there is no LDS staging and no barrier in the K loop.  The
-//    activation codes (a few KiB at these sizes) are copied to LDS once, or,
-//    for the fp16 entry point, quantized into LDS by the work-group itself
-//    (Sec. 4.3: the activation tile is quantized once and reused by both
-//    branches), with the same arithmetic as the quantizer kernel.
+// (m x r) and every work-group forms all of it itself, so no work-group waits
+// for another; the price is that each CU reads all of L1 (from L2, where the
+// first reader leaves it) in addition to its columns.
+//  * K is cut into pairs of 64-wide blocks, and a wavefront takes whole pairs:
+//    it reads the pair's activation operand once and multiplies it with the
+//    pair's operands of every rank tile and every column tile (or, with S = 2,
+//    with its half of the tiles).  So all sixteen wavefronts carry the same
+//    work whatever the rank, and the activation operand is shared by all tiles.
+//  * The residual sums stay in the wavefront's registers; the partial sums of
+//    the wavefronts are added in a fixed order at the end (the order of Y's
+//    fp32 accumulation is free; H's is not).
+//  * H is a chain over K: one fma per K-group, ascending.  The products that
+//    feed it come from different wavefronts, so they pass through LDS: a
+//    wavefront leaves I s_x (an exact fp32 value) of its pair there, and behind
+//    a barrier one thread per element of H walks the chunk's groups in
+//    ascending order with fma(I s_x, s_L1, h) -- the oracle's chain, so H is
+//    bit-identical.  A chunk is the pairs the sixteen wavefronts hold at once.
+//    The chain of one phase runs beside the products of the next (two buffers,
+//    where LDS holds them).
+//  * Weight and L1 operands stream from global memory straight into registers,
+//    one chunk (two for few tiles) ahead.  The activation codes (a few KiB at
+//    these sizes) are copied to LDS once, or, for the fp16 entry point,
+//    quantized into LDS by the work-group itself (Sec. 4.3: the activation tile
+//    is quantized once and reused by both branches), with the same arithmetic
+//    as the quantizer kernel.
 //
 // Products.  v_mfma_scale_f32_16x16x128_f8f6f4 on codes as fp8 subnormals
-// (block scales 2^9: exact integer sums).  A K-group pair spans the 128 K of
-// one product, and the two groups need separate sums:
-//  * up to 8 tokens, rows 0-7 take group A's codes in k < 64 and rows 8-15
-//    group B's in k >= 64 (zeros elsewhere), so one product yields both
-//    groups' sums; lanes 32-63 hold group B's and v_permlane32_swap brings
-//    them to lanes 0-31 for the chain;
-//  * up to 16 tokens, rows are tokens and two products take the pair's
-//    groups in turn (the other group's half of the operand zero).
-// Only the accumulator rows that hold real tokens (MV of the four per lane)
-// are rescaled, so single-token decode spends one fma per group and output
-// column, not sixteen.
+// (block scales 2^9: exact integer sums).  A pair spans the 128 K of one
+// product, and its two blocks need separate sums: rows 0-7 (up to 8 tokens)
+// take block A's codes in k < 64 and rows 8-15 block B's in k >= 64 (zeros
+// elsewhere), so one product yields both blocks' sums (A in lanes 0-31, B in
+// lanes 32-63).  Only the accumulator rows that hold real tokens (MV of the
+// four per lane) are rescaled.  9 to 16 tokens are two token blocks in the grid.
+//
+// What bounds it.  At these sizes a CU's vector ALU (a 4-bit operand takes 12
+// integer instructions of four cycles to expand, three quarters of a tile's
+// work) and its load path (64 bytes a clock: 2.3 MB per CU for 28672 -> 8192,
+// r = 128), neither hidden by the other for long behind the chunk's barrier.
+// Before, each rank tile of H was one wavefront's own chain, ~48 instructions
+// per pair one after the other, and its wavefront alone set the time.  us per
+// launch (one token unless said), before -> after: 4096 -> 4096, r = 64 10.8 ->
+// 8.5; 14336 -> 4096, r = 64 22.6 -> 15.6; 28672 -> 8192, r = 128 59.5 -> 52;
+// 8192 -> 28672, r = 128 5 tokens 45 -> 38; 14336 -> 4096, r = 64 8 tokens 41 ->
+// 22.  Tried and not kept: two pairs of a wavefront between barriers (no
+// change), non-temporal weight or L1 loads (2-20 % slower), the chain after the
+// products instead of ahead of them (8 % slower), a 16-token layout of two
+// products per tile (44 us where two token blocks take 27: its products and
+// codes fill the LDS, so nothing is double-buffered).
+
+#include <type_traits>
+
 #include "tq_device.hpp"
 #include "tq_kernels.hpp"
 
@@ -44,66 +64,80 @@ namespace {
 
 constexpr int DW = 16;                     // wavefronts per work-group
 constexpr int kDecodeXBytes = 112 * 1024;  // LDS for the activation codes
+constexpr int kDecodeLds = 160 * 1024;
 
-// Token layouts: MODE 1 / 2 / 4 put two K-groups in one product (rows are
-// (group, token) pairs, up to 8 tokens) with MV = MODE live accumulator rows
-// per lane; MODE 16 takes up to 16 tokens, one group per product.
+// Token layouts: MODE tokens (1, 2, or 4: up to 8) with MV = MODE live
+// accumulator rows per lane.
 template <int MODE>
 struct DMode {
-  static constexpr bool TOK8 = MODE != 16;
-  static constexpr int MV = MODE == 16 ? 4 : MODE;
+  static constexpr int MV = MODE;
   // LDS copy of the activation codes: fp8 operand bytes for one or two tokens,
   // TQ4 words (unpacked at use) otherwise; MX token slots per K-group
   static constexpr bool XFP8 = MODE <= 2;
-  static constexpr int MX = MODE == 16 ? 16 : (MODE <= 2 ? MODE : 8);
+  static constexpr int MX = MODE <= 2 ? MODE : 8;
   static constexpr int XB = XFP8 ? 64 : 32;   // bytes per (group, token)
-  // pairs of operands in flight per stage-1 wavefront, and the residual
-  // ring's budget in 16-byte fragments (what fits 128 registers unspilled)
-  static constexpr int D1 = MODE == 16 ? 8 : (MODE == 1 ? 9 : 10);
-  // one token: the two L1 scale rows of a pair arrive by one load (group A's
-  // row in lanes 0-31, group B's in lanes 32-63)
-  static constexpr bool MS = MODE == 1;
-  static constexpr int RF = MODE == 1 ? 10 : 8;
+  // rank tiles of a wavefront whose products share one phase's buffer (16 or 32 KiB)
+  static constexpr int PTM = 8 / MODE;
 };
 
-// A residual wavefront owns CTW of the work-group's CT column tiles (TG
-// tile groups) and keeps D2 pairs of their operands in flight.
-template <int CT, int RF> struct DRes {
-  static constexpr int CTW = CT == 1 ? 1 : 2;
-  static constexpr int TG = CT / CTW;
-  static constexpr int D2 = RF / CTW;
+// LDS layout (bytes).  K loop: the activation codes, their fp16 scales, NB
+// buffers of H products [rank tile][block][16 ranks][MX tokens] fp32, and NB of
+// L1 scales [group of the chunk][rank] fp16.  Epilogue, from the start: the
+// residual partials, H, Q_H and s_H.
+// R rank tiles and CT column tiles of a work-group.  S wavefronts share a pair
+// (each with its part of the tiles) where one would hold more operands and sums
+// than its 128 registers take.
+template <int MODE, int R, int CT>
+struct DCfg {
+  using MD = DMode<MODE>;
+  static constexpr int S = CT == 16 || (MODE > 2 && R >= 4 && R + CT > 10) ? 4
+                           : (R + CT > (MODE == 1 ? 10 : (MODE == 2 ? 8 : 5)) ? 2 : 1);
+  static constexpr int HS = R == 0 || R > S ? S : R;     // of these, with rank tiles of their own (the others repeat them)
+  static constexpr int HT = R / HS;                      // rank tiles of a wavefront
+  static constexpr int CW = CT > S ? CT / S : 1;         // column tiles (fewer than S: kept by the first)
+  static constexpr bool H = HT > 0;
+  static constexpr int PCH = DW / S;                     // pairs of a chunk
+  static constexpr int GL = 2 * PCH;                     // 64-wide blocks of a chunk
+  static constexpr int NT = HT + CW;                     // tiles of a wavefront
+  static constexpr int PD = NT + CW <= (MODE <= 2 ? 6 : 5) ? 2 : 1;   // chunks of operands in flight
+  static constexpr int PT = HT < MD::PTM ? HT : MD::PTM; // rank tiles of a phase
+  static constexpr int NPHASE = HT ? HT / PT : 0;
+  static constexpr int EPT = 16 * MD::MX;                // elements of a rank tile
+  static constexpr int EPS = PT * HS * EPT;              // elements of H of a phase
+  // H products: up to two tokens [element][block] (each thread of the chain
+  // reads its row 16 bytes at a time; rows padded so that neither side's lanes
+  // meet in a bank), else [block][element]; L1 scales [rank][row] or [row][rank]
+  static constexpr bool TR = MODE <= 2;
+  static constexpr int PS = TR ? GL + 4 : 1, PG = TR ? 1 : EPT;   // element and block strides, floats
+  static constexpr int SLS = GL + 8;                     // rank stride of the transposed scales
+  static constexpr int PBUF = PT * HS * EPT * (TR ? PS : GL) * 4;
+  static constexpr int NH = HT && NPHASE * EPS > 64 * DW ? NPHASE * EPS / (64 * DW) : 1;   // per thread
+  static constexpr int HSTR = kMaxRank + 1;              // fp32 per H row
+  static constexpr int QSTR = kMaxRank + 16;             // bytes per Q_H row
+  static constexpr int E_H = PCH * CT * 512;            // after the partials [PCH][CT][8][16] fp32
+  static constexpr int E_Q = E_H + 16 * HSTR * 4;
+  static constexpr int E_SH = E_Q + 16 * QSTR;
+  static constexpr int E_END = E_SH + 2 * 16 * 4;
+  static_assert(E_END <= kDecodeLds, "the epilogue fits");
 };
-
-// LDS layout (bytes): region 0 holds the activation codes during the K loop
-// and, aliased, the epilogue's residual partials, H, Q_H and s_H; the fp32
-// activation scales follow it.
 struct DLayout {
-  int xa, epi_res, epi_h, epi_q, epi_sh, xs, total;
-  static constexpr int HSTR = kMaxRank + 1;   // fp32 per H row
-  static constexpr int QSTR = kMaxRank + 16;  // bytes per Q_H row
-  // res_bytes: the residual partials [NPH][CT][16][16] fp32
-  __host__ __device__ DLayout(int kg, int mx, int xb, int res_bytes) {
+  int xs, p, sl, nb, total;
+  template <typename C>
+  __host__ __device__ static DLayout make(int kg, int r_pad32) {
     const int kgp = (kg + 1) / 2 * 2;
-    xa = kgp * mx * xb + 32;   // + a 32-byte zero pad
-    epi_res = 0;
-    epi_h = res_bytes;
-    epi_q = epi_h + 16 * HSTR * 4;
-    epi_sh = epi_q + 16 * QSTR;
-    const int epi_end = epi_sh + 2 * 16 * 4;
-    xs = ((xa > epi_end ? xa : epi_end) + 15) / 16 * 16;
-    total = xs + kgp * mx * 4;
+    DLayout L;
+    L.xs = (kgp * C::MD::MX * C::MD::XB + 32 + 15) / 16 * 16;   // + a 32-byte zero pad
+    L.p = (L.xs + (kgp + 1) * C::MD::MX * 2 + 15) / 16 * 16;   // + a row of zeros
+    const int buf = C::PBUF + (C::H ? r_pad32 * (C::TR ? C::SLS : C::GL) * 2 : 0);
+    L.nb = L.p + 2 * buf <= kDecodeLds ? 2 : 1;
+    L.sl = L.p + L.nb * C::PBUF;
+    const int k_end = L.p + L.nb * buf;
+    L.total = k_end > C::E_END ? k_end : C::E_END;
+    return L;
   }
 };
 
 __host__ __device__ inline int rank_tiles(int r) { return (r + 15) / 16; }
-
-// The K-loop roles: wavefronts 0 .. R - 1 form H, the others the residual.
-template <int MODE, int CT>
-__host__ __device__ inline DLayout decode_layout(int kg, int r) {
-  using DR = DRes<CT, DMode<MODE>::RF>;
-  const int nph = (DW - rank_tiles(r)) / DR::TG;
-  return DLayout(kg, DMode<MODE>::MX, DMode<MODE>::XB, nph * CT * 1024);
-}
 
 // max over runs of n = 8, 16 or 32 aligned lanes, in every lane of the run
 __device__ __forceinline__ float dpp_max(float a, int ctrl_sel) {
@@ -144,427 +178,507 @@ __device__ __forceinline__ v8i lds_v8i(const uint8_t *p) {
   return v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
 }
 
-__device__ __forceinline__ float lo_half(uint32_t w) { return half_bits_to_float((uint16_t)(w & 0xffffu)); }
-__device__ __forceinline__ float hi_half(uint32_t w) { return half_bits_to_float((uint16_t)(w >> 16)); }
+__device__ __forceinline__ _Float16 half_of(uint32_t w, int hi) {
+  return __builtin_bit_cast(_Float16, (uint16_t)(hi ? w >> 16 : w & 0xffffu));
+}
 
-// Operands of one K-group pair: for a stage-1 wavefront the fragment of its
-// rank tile with the L1 scales of both groups, for a residual wavefront the
-// CT weight fragments with their scales.
-struct S1Slot {
-  u32x4 l1;
-  // fp16 L1 scales of the lane's rank for groups A and B; for one token a
-  // single load, the lane's own group's row (sla only)
-  uint32_t sla, slb;
-};
-template <int CTW>
-struct ResSlot {
-  u32x4 w[CTW];
-  uint32_t swa[CTW], swb[CTW];   // fp16 weight scales (TOK8: the lane's own group in swa)
-};
+// every LDS access of this wavefront so far has completed, then the work-group
+// barrier (global loads into registers stay in flight across it)
+__device__ __forceinline__ void d_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
 
-// GK: 64-wide K blocks per quantization group (1 or 2, the layer's geo.gk),
-// or 0: read from geo.gk at run time
-template <int MODE, int CT, bool FQ, int GK>
+// Raw buffer of `bytes` bytes at a wave-uniform address: loads past its end
+// return zeros (and read nothing), so operands past K need no test.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t d_buffer(const uint8_t *p, uint32_t bytes) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(((uint64_t)hi << 32) | lo), 0,
+                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+__device__ __forceinline__ u32x4 d_load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
+}
+__device__ __forceinline__ uint32_t d_load2(__amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b16(rsrc, off, 0, 0);
+}
+
+template <int MODE, int R, int CT>
 __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
                                                                    const uint16_t *__restrict__ xh) {
+  using C = DCfg<MODE, R, CT>;
   using MD = DMode<MODE>;
-  constexpr int MX = MD::MX, MV = MD::MV, XB = MD::XB;
+  constexpr int MX = MD::MX, MV = MD::MV, XB = MD::XB, PCH = C::PCH, GL = C::GL;
+  constexpr int S = C::S, HT = C::HT, CW = C::CW;
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const Geometry &geo = a.geo;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int q = lane >> 4, c16 = lane & 15, qh = q & 1;
-  const int KG = geo.k / kGroup, NP = (KG + 1) / 2;
-  const int m = a.m;
-  const int r = geo.r, R = rank_tiles(r);
-  const int NS = R;   // stage-1 wavefronts
-  const int NRES = DW - NS;
+  const int q = lane >> 4, c16 = lane & 15, qh = q & 1, gq = q >> 1;
+  const int KG = geo.k / kGroup, NP = (KG + 1) / 2, NCH = (NP + PCH - 1) / PCH;
+  // Column block and token block (8 tokens from m0 on, m of them live).  Two
+  // token blocks read the same weights: work-groups are dealt round-robin to
+  // the 8 XCDs, so the two of a column block are placed on one, whose L2 then
+  // serves the second.
+  int cblk = blockIdx.x, m0 = 0;
+  if (a.m > 8) {
+    const int nwg = gridDim.x, per = nwg / 8, rem = nwg % 8, x = blockIdx.x % 8, i = blockIdx.x / 8;
+    const int logical = (x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per) + i;
+    cblk = logical / 2;
+    m0 = logical % 2 * 8;
+  }
+  const int m = min(a.m - m0, 8);
+  const int r = geo.r, gk = geo.gk;
   const int ct16 = geo.n_pad / 16;
-  const int c0 = blockIdx.x * CT;
-  const DLayout LY = decode_layout<MODE, CT>(KG, r);
+  const int c0 = cblk * CT;
+  const DLayout LY = DLayout::make<C>(KG, geo.r_pad32);
   uint8_t *XA = smem;
-  float *XS = reinterpret_cast<float *>(smem + LY.xs);
-  const uint8_t *wcodes = a.packed + geo.off_w;
-  const uint16_t *wscales = reinterpret_cast<const uint16_t *>(a.packed + geo.off_ws);
-  const uint8_t *l1codes = a.packed + geo.off_l1;
-  const uint16_t *l1scales = reinterpret_cast<const uint16_t *>(a.packed + geo.off_l1s);
-  const uint8_t *l2codes = a.packed + geo.off_l2;
+  uint16_t *XS = reinterpret_cast<uint16_t *>(smem + LY.xs);
   const uint16_t *l2scales = reinterpret_cast<const uint16_t *>(a.packed + geo.off_l2s);
 
-  // ---- roles: wavefront w < R forms rank tile w of H over every pair; the
-  // others are residual wavefronts: rslot = w - R owns tile group rslot % TG
-  // and the pairs rslot / TG + i NPH ----
-  using DR = DRes<CT, MD::RF>;
-  constexpr int D1 = MD::D1;
-  constexpr int CTW = DR::CTW, TG = DR::TG, D2 = DR::D2;
-  const bool s1 = wave < NS;
-  const int rslot = wave - NS;
-  const int NPH = NRES / TG;
-  const int tg = s1 ? 0 : rslot % TG, ph = s1 ? 0 : rslot / TG;
-  const bool rbusy = !s1 && ph < NPH;
-  const int nres_it = rbusy && ph < NP ? (NP - ph + NPH - 1) / NPH : 0;
-  const int ctw0 = c0 + tg * CTW;   // first column tile of this residual wavefront
-
-  // Ring loads are unconditional (a pair past the end reloads the last one),
-  // so the compiler can count the outstanding loads and wait only for the
-  // slot it uses.  Lane quarters q < 2 take group A = 2p, q >= 2 group B.
-  // Addresses are a wave-uniform base (pair p) plus a fixed 32-bit lane
-  // offset, kept to a few scalar operations per load: the scalar unit, which
-  // all wavefronts of a CU share, is what a costlier form saturates first.
-  // On an odd tail (group 2p + 1 == KG) the group-B lanes read the zero codes
-  // and zero scale row that follow each section in the packed buffer.
-  // (Section offsets fit 32 bits: the packed buffer is below 4 GiB.)
-  const int gq = q >> 1;
-  const uint32_t l1_lane = (uint32_t)(((wave >> 1) * KG * 64 + gq * 64 + qh * 32 + (wave & 1) * 16 + c16) * 16);
-  const uint32_t l1s_lane = (uint32_t)(16 * wave + c16) * 2;
-  // Scale rows: one per quantization group, so a pair of 64-wide blocks spans
-  // two rows (64-wide groups) or one (128-wide groups, gk = 2), and group B's
-  // row is the next one or the same.
-  const int gk = GK ? GK : geo.gk;
-  const uint32_t l1s_pair = (uint32_t)geo.r_pad32 * 4 / gk, ws_pair = (uint32_t)geo.n_pad * 4 / gk;
-  const uint32_t l1s_b = gk == 1 ? (uint32_t)geo.r_pad32 * 2 : 0u, ws_b = gk == 1 ? (uint32_t)geo.n_pad * 2 : 0u;
-  const uint8_t *l1sb = reinterpret_cast<const uint8_t *>(l1scales);
-  const uint8_t *wsb = reinterpret_cast<const uint8_t *>(wscales);
-  const uint32_t l1s_own = l1s_lane + gq * l1s_b;   // the lane's own group's row
-  auto load_s1 = [&](S1Slot &S, int p) {
-    S.l1 = *reinterpret_cast<const u32x4 *>(l1codes + (uint32_t)(p * 2048) + l1_lane);
-    const uint8_t *sb = l1sb + (uint32_t)p * l1s_pair;
-    if constexpr (MD::MS) {
-      S.sla = *reinterpret_cast<const uint16_t *>(sb + l1s_own);
-    } else {
-      S.sla = *reinterpret_cast<const uint16_t *>(sb + l1s_lane);
-      S.slb = *reinterpret_cast<const uint16_t *>(sb + l1s_b + l1s_lane);
-    }
-  };
-  uint32_t w_lane[CTW], ws_lane[CTW];
-  const uint32_t ws_gq = gq * ws_b;   // the lane's own block's group (TOK8)
+  // ---- this wavefront's pairs (pl of every chunk) and tiles ----
+  const int sub = wave % S, pl = wave / S;
+  const int hsub = sub % C::HS;
+  const int rt0 = hsub * HT;                     // first rank tile
+  const int ctw0 = c0 + sub % CT * CW;           // first column tile
+  // Lane quarters q < 2 take block A = 2p of a pair, q >= 2 block B.  On an
+  // odd tail (2p + 1 == KG), and past K, the loads return zeros.
+  __amdgpu_buffer_rsrc_t tbuf[C::NT];
 #pragma unroll
-  for (int j = 0; j < CTW; j++) {
-    const int ct = min(ctw0 + j, ct16 - 1);
-    w_lane[j] = (uint32_t)((((ct >> 1) * KG + gq) * 64 + qh * 32 + (ct & 1) * 16 + c16) * 16);
+  for (int j = 0; j < HT; j++) {
+    const int t = rt0 + j, half = (t & 1) * 256;
+    tbuf[j] = d_buffer(a.packed + geo.off_l1 + (int64_t)(t >> 1) * KG * 1024 + half, (uint32_t)KG * 1024u - half);
+  }
+  uint32_t ws_lane[CW];
+#pragma unroll
+  for (int j = 0; j < CW; j++) {
+    const int ct = min(ctw0 + j, ct16 - 1), half = (ct & 1) * 256;   // past the last tile: never stored
+    tbuf[HT + j] = d_buffer(a.packed + geo.off_w + (int64_t)(ct >> 1) * KG * 1024 + half, (uint32_t)KG * 1024u - half);
     ws_lane[j] = (uint32_t)(16 * ct + c16) * 2;
   }
-  auto load_res = [&](ResSlot<CTW> &S, int p) {
-    const uint8_t *sa = wsb + (uint32_t)p * ws_pair;
+  // scale rows: one per quantization group (gk blocks)
+  const int KQ = KG / gk;
+  const auto wsbuf = d_buffer(a.packed + geo.off_ws, (uint32_t)KQ * (uint32_t)geo.n_pad * 2u);
+  const uint32_t ws_row = (uint32_t)geo.n_pad * 2u;
+  struct Slot {
+    u32x4 b[C::NT];
+    uint32_t sw[CW];   // fp16 weight scales of the lane's own block
+  };
+  const uint32_t code_lane = (uint32_t)(gq * 1024 + qh * 512 + c16 * 16);
+  // offsets of the next pair to load, which advance chunk by chunk
+  uint32_t code_off = (uint32_t)pl * 2048u + code_lane;
+  const uint32_t ws_b = gk == 1 ? ws_row : 0u;   // block B's row: the next one, or the same group's
+  uint32_t ws_off = (uint32_t)(2 * pl / gk) * ws_row + (gq ? ws_b : 0u);
+  const uint32_t ws_step = (uint32_t)(GL / gk) * ws_row;
+  auto load_tile = [&](Slot &Q, int j) { Q.b[j] = d_load16(tbuf[j], code_off); };
+  auto load_scales = [&](Slot &Q) {   // and on to the next pair
 #pragma unroll
-    for (int j = 0; j < CTW; j++) {
-      S.w[j] = *reinterpret_cast<const u32x4 *>(wcodes + (uint32_t)(p * 2048) + w_lane[j]);
-      if constexpr (MD::TOK8) {
-        S.swa[j] = *reinterpret_cast<const uint16_t *>(sa + (ws_lane[j] + ws_gq));
+    for (int j = 0; j < CW; j++) Q.sw[j] = d_load2(wsbuf, ws_off + ws_lane[j]);
+    code_off += PCH * 2048u;
+    ws_off += ws_step;
+  };
+
+  // ---- L1 scales of a chunk: its GL / gk rows, 16 bytes (8 ranks) a thread,
+  // as they lie or transposed (lanes along the rows then) ----
+  const int sl_rows = GL / gk;
+  const int sl_row = C::TR ? tid % GL : tid / (geo.r_pad32 / 8 > 0 ? geo.r_pad32 / 8 : 1);
+  const int sl_part = C::TR ? tid / GL : tid % (geo.r_pad32 / 8 > 0 ? geo.r_pad32 / 8 : 1);
+  const bool sl_live = HT && sl_row < sl_rows && sl_part < geo.r_pad32 / 8;
+  const auto slbuf = d_buffer(a.packed + geo.off_l1s, HT ? (uint32_t)KQ * (uint32_t)geo.r_pad32 * 2u : 0u);
+  u32x4 slreg = {0u, 0u, 0u, 0u};
+  uint32_t sl_off = (uint32_t)sl_row * (uint32_t)geo.r_pad32 * 2u + (uint32_t)sl_part * 16u;
+  auto sl_load = [&]() {   // and on to the next chunk
+    slreg = d_load16(slbuf, sl_off);
+    sl_off += (uint32_t)(sl_rows * geo.r_pad32 * 2);
+  };
+  const int sl_buf = geo.r_pad32 * (C::TR ? C::SLS : GL) * 2;
+  auto sl_write = [&](int c) {
+    if (sl_live) {
+      uint8_t *B = smem + LY.sl + (LY.nb == 2 ? (c & 1) * sl_buf : 0);
+      if constexpr (C::TR) {
+        uint16_t *D = reinterpret_cast<uint16_t *>(B) + sl_part * 8 * C::SLS + sl_row;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          D[2 * e * C::SLS] = (uint16_t)(slreg[e] & 0xffffu);
+          D[(2 * e + 1) * C::SLS] = (uint16_t)(slreg[e] >> 16);
+        }
       } else {
-        S.swa[j] = *reinterpret_cast<const uint16_t *>(sa + ws_lane[j]);
-        S.swb[j] = *reinterpret_cast<const uint16_t *>(sa + ws_b + ws_lane[j]);
+        *reinterpret_cast<u32x4 *>(B + (sl_row * geo.r_pad32 + sl_part * 8) * 2) = slreg;
       }
     }
   };
 
-  // ---- the activation codes and scales into LDS (each wavefront runs this
-  // once, after issuing the first loads of its own ring) ----
+  // ---- fp16 activations to quantize: eight lanes per (token, quantization
+  // group), eight values of each of its blocks, XI items of a thread ahead.
+  // Their loads go first: loads return in order, and the first barrier waits
+  // for these ----
+  constexpr int XI = 2;
+  const int nitem = m * KQ, xe = lane & 7;
+  constexpr int XSTEP = 64 * DW / 8;              // items of one pass of the work-group
+  // (token, quantization group) of this thread's next item to load and to
+  // quantize, stepped without a division
+  const int xdt = XSTEP / KQ, xdg = XSTEP % KQ;
+  struct XPos {
+    int t, g;
+  };
+  auto x_next = [&](XPos &p) {
+    p.t += xdt;
+    p.g += xdg;
+    if (p.g >= KQ) {
+      p.g -= KQ;
+      p.t++;
+    }
+  };
+  u32x4 xr0[XI], xr1[XI];
+  XPos xl = {tid / 8 / KQ, tid / 8 % KQ}, xq = xl;
+  auto x_load = [&](int it0) {   // past the last item: item 0, not written
+#pragma unroll
+    for (int i = 0; i < XI; i++) {
+      if (it0 + i * XSTEP >= nitem) break;
+      const bool live = xl.t < m;
+      const uint16_t *src = xh + (int64_t)(m0 + (live ? xl.t : 0)) * geo.k + (live ? xl.g * gk : 0) * kGroup + 8 * xe;
+      xr0[i] = *reinterpret_cast<const u32x4 *>(src);
+      if (gk == 2) xr1[i] = *reinterpret_cast<const u32x4 *>(src + kGroup);
+      x_next(xl);
+    }
+  };
+  // quantized activations: a thread's first 16-byte fragment (block, token,
+  // half) of tile 0's TQ4 blocks and its first scale, ahead likewise
+  const int nfrag = KG * m * 2, nxs = (2 * NP + 1) * MX;
+  auto frag = [&](int f) {
+    const int g = f / (2 * m), t = (f / 2) % m, h = f & 1;
+    return *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(a.xc) + ((int64_t)g * 64 + 32 * h + m0 + t) * 16);
+  };
+  auto xscale = [&](int idx) {   // zeros past m and past K
+    const int g = idx / MX, t = idx % MX;
+    return g < KG && t < m ? a.xs[(int64_t)(g / gk) * a.ms + m0 + t] : (uint16_t)0;
+  };
+  u32x4 frag0 = {0u, 0u, 0u, 0u};
+  uint16_t xscale0 = 0;
+  if (xh != nullptr) {
+    x_load(0);
+  } else {
+    if (tid < nfrag) frag0 = frag(tid);
+    if (tid < nxs) xscale0 = xscale(tid);
+  }
+
+  // ---- first loads: operands of the first chunks, stage-2 operands of the
+  // storing wavefronts, L1 scales ----
+  Slot ring[C::PD];
+#pragma unroll
+  for (int u = 0; u < C::PD; u++) {
+#pragma unroll
+    for (int j = 0; j < C::NT; j++) load_tile(ring[u], j);
+    load_scales(ring[u]);
+  }
+  if constexpr (HT > 0) sl_load();
+  const int RB = (r + 63) / 64;   // 64-rank blocks of stage 2 (<= 2)
+  const int ct_out = min(c0 + (wave < CT ? wave : 0), ct16 - 1);
+  u32x4 l2raw = {0u, 0u, 0u, 0u};
+  uint32_t l2sa = 0, l2sb = 0;
+  const int hg1 = r > 0 ? 64 / geo.gr : 0;   // rank group of the second 64-rank block (0 if gr = 128)
+  if (HT > 0 && wave < CT) {
+    const int rbq = min(gq, RB - 1), L = qh * 32 + (ct_out & 1) * 16 + c16;
+    l2raw = *reinterpret_cast<const u32x4 *>(
+        a.packed + geo.off_l2 + (((int64_t)(ct_out >> 1) * (geo.r_pad64 / 64) + rbq) * 64 + L) * 16);
+    l2sa = l2scales[ct_out * 16 + c16];
+    l2sb = RB > 1 ? l2scales[(int64_t)hg1 * geo.n_pad + ct_out * 16 + c16] : 0u;
+  }
+
+  // ---- the activation codes and scales into LDS ----
   const int KGP = 2 * NP;
-  auto prologue = [&]() {
-    if constexpr (FQ) {
-      // eight lanes per (token, quantization group), eight values of each of
-      // the group's gk 64-wide blocks; the steps are those of the quantizer
-      // kernel, so the codes and scales are the same bits
-      const int e = lane & 7;
-      const int KQ = KG / gk;
-      const int nitem = m * KQ;
-      for (int it0 = 0; it0 < nitem; it0 += 64 * DW / 8) {
-        const int it = it0 + tid / 8;
-        const bool live = it < nitem;
-        const int t = live ? it / KQ : 0, g0 = live ? it % KQ * gk : 0, g1 = g0 + gk - 1;
-        const uint16_t *src = xh + (int64_t)t * geo.k + 8 * e;
-        const u32x4 raw0 = *reinterpret_cast<const u32x4 *>(src + g0 * kGroup);
-        u32x4 raw1 = raw0;
-        if (gk == 2) raw1 = *reinterpret_cast<const u32x4 *>(src + g1 * kGroup);
+  if (xh != nullptr) {
+    // the steps of the quantizer kernel, so the codes and scales are the same bits
+    for (int it0 = 0; it0 < nitem; it0 += XI * XSTEP) {
+      if (it0 > 0) x_load(it0);
+#pragma unroll
+      for (int i = 0; i < XI; i++) {
+        if (it0 + i * XSTEP >= nitem) break;
+        const int t = xq.t, g0 = xq.g * gk;
+        const bool live = t < m;
+        x_next(xq);
         float v0[8], v1[8];
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-          v0[2 * i] = half_bits_to_float((uint16_t)(raw0[i] & 0xffffu));
-          v0[2 * i + 1] = half_bits_to_float((uint16_t)(raw0[i] >> 16));
-          v1[2 * i] = half_bits_to_float((uint16_t)(raw1[i] & 0xffffu));
-          v1[2 * i + 1] = half_bits_to_float((uint16_t)(raw1[i] >> 16));
+        for (int e = 0; e < 4; e++) {
+          v0[2 * e] = half_bits_to_float((uint16_t)(xr0[i][e] & 0xffffu));
+          v0[2 * e + 1] = half_bits_to_float((uint16_t)(xr0[i][e] >> 16));
         }
         float amax = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 8; i++) amax = fmaxf(amax, fmaxf(fabsf(v0[i]), fabsf(v1[i])));
+        for (int e = 0; e < 8; e++) amax = fmaxf(amax, fabsf(v0[e]));
+        if (gk == 2) {
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            v1[2 * e] = half_bits_to_float((uint16_t)(xr1[i][e] & 0xffffu));
+            v1[2 * e + 1] = half_bits_to_float((uint16_t)(xr1[i][e] >> 16));
+          }
+#pragma unroll
+          for (int e = 0; e < 8; e++) amax = fmaxf(amax, fabsf(v1[e]));
+        }
         amax = max8_dpp(amax);
         uint16_t s16;
         const float sc = q4_scale(amax, s16);
         const float y = sc == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(sc);
-#pragma unroll
-        for (int b = 0; b < 2; b++) {
-          if (b == 1 && gk == 1) break;
+        auto put = [&](const float (&v)[8], int g) {
           uint32_t b0, b1;
-          quant8_fp8(b == 0 ? v0 : v1, sc, y, b0, b1);
-          const int g = b == 0 ? g0 : g1;
+          quant8_fp8(v, sc, y, b0, b1);
           if (live) {
             uint8_t *dst = XA + (g * MX + t) * XB;
             if constexpr (MD::XFP8)
-              *reinterpret_cast<uint2 *>(dst + 8 * e) = make_uint2(b0, b1);
+              *reinterpret_cast<uint2 *>(dst + 8 * xe) = make_uint2(b0, b1);
             else
-              *reinterpret_cast<uint32_t *>(dst + 4 * e) = b0 | __builtin_amdgcn_alignbit(b1, b1, 28);
-            if (e == 0) XS[g * MX + t] = sc;
+              *reinterpret_cast<uint32_t *>(dst + 4 * xe) = b0 | __builtin_amdgcn_alignbit(b1, b1, 28);
+            if (xe == 0) XS[g * MX + t] = s16;
           }
-        }
-      }
-      for (int idx = tid; idx < KGP * MX; idx += 64 * DW)
-        if (idx / MX >= KG || idx % MX >= m) XS[idx] = 0.0f;
-    } else {
-      // 16-byte fragments (group g, token t, half h) of tile 0's TQ4 blocks
-      const uint8_t *xc = reinterpret_cast<const uint8_t *>(a.xc);
-      const int nfrag = KG * m * 2;
-      for (int f = tid; f < nfrag; f += 64 * DW) {
-        const int g = f / (2 * m), t = (f / 2) % m, h = f & 1;
-        const u32x4 raw = *reinterpret_cast<const u32x4 *>(xc + ((int64_t)g * 64 + 32 * h + t) * 16);
-        uint8_t *dst = XA + (g * MX + t) * XB;
-        if constexpr (MD::XFP8) {
-          const v8i o = unpack32(raw);
-          *reinterpret_cast<u32x4 *>(dst + 32 * h) = u32x4{(uint32_t)o[0], (uint32_t)o[1], (uint32_t)o[2], (uint32_t)o[3]};
-          *reinterpret_cast<u32x4 *>(dst + 32 * h + 16) = u32x4{(uint32_t)o[4], (uint32_t)o[5], (uint32_t)o[6], (uint32_t)o[7]};
-        } else {
-          *reinterpret_cast<u32x4 *>(dst + 16 * h) = raw;
-        }
-      }
-      for (int idx = tid; idx < KGP * MX; idx += 64 * DW) {
-        const int g = idx / MX, t = idx % MX;
-        XS[idx] = g < KG && t < m ? half_bits_to_float(a.xs[(int64_t)(g / gk) * a.ms + t]) : 0.0f;
+        };
+        put(v0, g0);
+        if (gk == 2) put(v1, g0 + 1);
       }
     }
-    // zero codes for the token slots past m, the odd tail group and the pad
-    // that lanes outside the operand's live rows read
-    for (int idx = tid; idx < KGP * MX * XB / 16 + 2; idx += 64 * DW) {
-      const int e = idx * 16;
-      const int g = e / (MX * XB), t = (e / XB) % MX;
-      if (idx >= KGP * MX * XB / 16 || g >= KG || t >= m)
-        *reinterpret_cast<u32x4 *>(XA + e) = u32x4{0u, 0u, 0u, 0u};
+    for (int idx = tid; idx < (KGP + 1) * MX; idx += 64 * DW)
+      if (idx / MX >= KG || idx % MX >= m) XS[idx] = 0;
+  } else {
+    for (int f = tid; f < nfrag; f += 64 * DW) {
+      const int g = f / (2 * m), t = (f / 2) % m, h = f & 1;
+      const u32x4 raw = f < 64 * DW ? frag0 : frag(f);
+      uint8_t *dst = XA + (g * MX + t) * XB;
+      if constexpr (MD::XFP8) {
+        const v8i o = unpack32(raw);
+        *reinterpret_cast<u32x4 *>(dst + 32 * h) = u32x4{(uint32_t)o[0], (uint32_t)o[1], (uint32_t)o[2], (uint32_t)o[3]};
+        *reinterpret_cast<u32x4 *>(dst + 32 * h + 16) = u32x4{(uint32_t)o[4], (uint32_t)o[5], (uint32_t)o[6], (uint32_t)o[7]};
+      } else {
+        *reinterpret_cast<u32x4 *>(dst + 16 * h) = raw;
+      }
     }
-    __syncthreads();
-  };
+    for (int idx = tid; idx < nxs; idx += 64 * DW) XS[idx] = idx < 64 * DW ? xscale0 : xscale(idx);
+  }
+  // zero codes for the token slots past m, the odd tail block and the pad that
+  // lanes outside the operand's live rows read
+  for (int idx = tid; idx < KGP * MX * XB / 16 + 2; idx += 64 * DW) {
+    const int e = idx * 16;
+    const int g = e / (MX * XB), t = (e / XB) % MX;
+    if (idx >= KGP * MX * XB / 16 || g >= KG || t >= m)
+      *reinterpret_cast<u32x4 *>(XA + e) = u32x4{0u, 0u, 0u, 0u};
+  }
+  d_barrier();
 
-  // activation operand of pair p: lanes outside the operand's live rows
-  // (TOK8: group A lives in rows 0-7 of quarters 0-1, group B in rows 8-15
-  // of quarters 2-3) or past the MX token slots read the zero pad after the
-  // codes; the others read their (group 2p + gq, token, half) slot, zero
-  // past m and past the last K-group
+  // Activation operand of pair p: lanes outside the operand's live rows (block
+  // A lives in rows 0-7 of quarters 0-1, block B in rows 8-15 of quarters 2-3;
+  // one and two tokens twice in each eight), past the MX token slots or past K
+  // read the zero pad after the codes; the others their (block 2p + gq, token,
+  // half) slot, zero past m.
   const int arow = lane & 15;
-  const int atok = MD::TOK8 ? (arow & 7) : arow;
-  const bool alive = (MD::TOK8 ? ((arow < 8) == (q < 2)) : true) && atok < MX;
+  const int atok = MODE <= 2 ? (arow & 3) : (arow & 7);
   const int xpad = KGP * MX * XB;
-  const int abase = alive ? (gq * MX + atok) * XB + qh * (XB / 2) : xpad;
-  const int astride = alive ? 2 * MX * XB : 0;
   auto act_op = [&](int p) -> v8i {
-    const uint8_t *src = XA + abase + p * astride;
+    const bool alive = (arow < 8) == (q < 2) && atok < MX && p < NP;
+    const uint8_t *src = XA + (alive ? ((2 * p + gq) * MX + atok) * XB + qh * (XB / 2) : xpad);
     if constexpr (MD::XFP8) return lds_v8i(src);
     else return unpack32(*reinterpret_cast<const u32x4 *>(src));
   };
-  // token of accumulator row v of this lane, clamped into the LDS slots
-  auto tok_of = [&](int v) {
-    const int t = MD::TOK8 ? 4 * qh + v : 4 * q + v;
-    return t < MX ? t : 0;
+  // the fp16 activation scales of this lane's accumulator rows (consecutive
+  // tokens) for block g, as one or two words; zero past K
+  struct Sx {
+    uint32_t w0, w1;
   };
-  const v8i z8 = {0, 0, 0, 0, 0, 0, 0, 0};
-
-  float hacc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  v4f acc[CTW];
-#pragma unroll
-  for (int j = 0; j < CTW; j++) acc[j] = v4f{0, 0, 0, 0};
-
-  // the activation scales of this lane's accumulator rows for group g (the
-  // rows are consecutive tokens, so one LDS read)
-  auto xs_row = [&](int g) -> v4f {
-    const float *p = XS + g * MX + tok_of(0);
-    if constexpr (MV == 1) return v4f{p[0], 0.0f, 0.0f, 0.0f};
-    else if constexpr (MV == 2) { const float2 t = *reinterpret_cast<const float2 *>(p); return v4f{t.x, t.y, 0.0f, 0.0f}; }
-    else return *reinterpret_cast<const v4f *>(p);
-  };
-
-  // Stage 1, software-pipelined three deep so that no step waits on the one
-  // before it: the LDS operands of pair i + 2 are read, the matrix product of
-  // pair i + 1 is issued, and the chain step of pair i runs, in that order.
-  // The chain is the ascending-group fma of rank tile `wave` (gb == KG on an
-  // odd tail: zero codes and scales, so that step adds exactly nothing).
-  struct S1Lds {
-    v8i av;          // activation operand
-    v4f sxa, sxb;    // activation scales of the lane's rows, groups A and B
-  };
-  struct S1Prod {
-    v4f I;           // integer sums (TOK8: group A in lanes 0-31, B in 32-63)
-    v4f I2;          // 16-token layout: group B's sums
-    v4f sxa, sxb;
-    uint32_t sla, slb;   // one token: the L1 scales of groups A and B for lanes 0-31
-  };
-  auto s1_lds = [&](int p) -> S1Lds {
-    S1Lds r;
-    r.av = act_op(p);
-    r.sxa = xs_row(2 * p);
-    r.sxb = xs_row(2 * p + 1);
-    return r;
-  };
-  auto s1_mfma = [&](const S1Lds &A, const S1Slot &Sl) -> S1Prod {
-    S1Prod r;
-    const v8i b = unpack32(Sl.l1);
-    if constexpr (MD::TOK8) {
-      r.I = mfma_codes_16x16x128(A.av, b);
-      r.I2 = v4f{0, 0, 0, 0};
+  auto xs_row = [&](int g) -> Sx {
+    const uint16_t *p = XS + min(g, KGP) * MX + (4 * qh < MX ? 4 * qh : 0);
+    Sx s = {0u, 0u};
+    if constexpr (MV == 1) {
+      s.w0 = *p;
+    } else if constexpr (MV == 2) {
+      s.w0 = *reinterpret_cast<const uint32_t *>(p);
     } else {
-      r.I = mfma_codes_16x16x128(q < 2 ? A.av : z8, b);
-      r.I2 = mfma_codes_16x16x128(q < 2 ? z8 : A.av, b);
+      const uint2 t = *reinterpret_cast<const uint2 *>(p);
+      s.w0 = t.x;
+      s.w1 = t.y;
     }
-    r.sxa = A.sxa;
-    r.sxb = A.sxb;
-    // group B's scale comes from lanes 32-63, as its sums do (with 128-wide
-    // groups both halves read the same row and only sla is used)
-    r.sla = Sl.sla;
-    r.slb = MD::MS && GK != 2 ? __builtin_bit_cast(uint32_t, upper_half(__builtin_bit_cast(float, Sl.sla))) : 0u;
-    return r;
+    return s;
   };
-  // One chain step per group: h = fma(I s_x, s_L1, h).  I s_x is exact in
-  // fp32 (|I| < 2^12 times an 11-bit fp16 significand), so this rounds the
-  // same exact value I s_x s_L1 + h once, as fma(I, s_x s_L1, h) does; the
-  // fp16 scale enters the fma without a separate conversion.
-  auto s1_chain = [&](const S1Prod &P, const S1Slot &Sl) {
-    const _Float16 sla = __builtin_bit_cast(_Float16, (uint16_t)(MD::MS ? P.sla : Sl.sla));
-    const _Float16 slb = __builtin_bit_cast(_Float16, (uint16_t)(MD::MS ? P.slb : Sl.slb));
+  // I s_x of the lane's rows: exact in fp32 (|I| < 2^12 times an 11-bit
+  // significand), so fma(I s_x, s_L1, h) rounds the same exact value once as
+  // fma(I, s_x s_L1, h) does
+  auto times_sx = [&](v4f I, Sx s) -> v4f {
+    v4f t = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int v = 0; v < MV; v++) {
-      const float ib = MD::TOK8 ? upper_half(P.I[v]) : P.I2[v];
-      if constexpr (GK == 2) {
-        // a 128-wide group: its two halves' sums add exactly (|I| < 2^13)
-        // into the group's one step
-        hacc[v] = fmaf((P.I[v] + ib) * P.sxa[v], (float)sla, hacc[v]);
-      } else if constexpr (GK == 1) {
-        hacc[v] = fmaf(P.I[v] * P.sxa[v], (float)sla, hacc[v]);
-        hacc[v] = fmaf(ib * P.sxb[v], (float)slb, hacc[v]);
-      } else {
-        // the same, chosen at run time: for a 128-wide group the second step
-        // adds +0, which leaves the (never negative-zero) h as is
-        const float i1 = gk == 2 ? P.I[v] + ib : P.I[v];
-        const float i2 = gk == 2 ? 0.0f : ib;
-        hacc[v] = fmaf(i1 * P.sxa[v], (float)sla, hacc[v]);
-        hacc[v] = fmaf(i2 * P.sxb[v], (float)slb, hacc[v]);
-      }
-    }
+    for (int v = 0; v < MV; v++) t[v] = fmaf(I[v], (float)half_of(v < 2 ? s.w0 : s.w1, v & 1), 0.0f);
+    return t;
   };
-  auto residual = [&](const ResSlot<CTW> &Sl, int p) {
-    const int ga = 2 * p, gb = 2 * p + 1;
-    const v8i av = act_op(p);
-    const v4f sxa = xs_row(ga), sxb = xs_row(gb);
+
+  v4f acc[CW];
 #pragma unroll
-    for (int j = 0; j < CTW; j++) {
-      const v8i b = unpack32(Sl.w[j]);
-      if constexpr (MD::TOK8) {
-        const v4f I = mfma_codes_16x16x128(av, b);
-        const _Float16 sw = __builtin_bit_cast(_Float16, (uint16_t)Sl.swa[j]);
-        const v4f sx = q < 2 ? sxa : sxb;   // the lane's own group
+  for (int j = 0; j < CW; j++) acc[j] = v4f{0, 0, 0, 0};
+  float h[C::NH];
 #pragma unroll
-        for (int v = 0; v < MV; v++) acc[j][v] = fmaf(I[v] * sx[v], (float)sw, acc[j][v]);
-      } else {
-        const v4f I1 = mfma_codes_16x16x128(q < 2 ? av : z8, b);
-        const v4f I2 = mfma_codes_16x16x128(q < 2 ? z8 : av, b);
-        const _Float16 swa = __builtin_bit_cast(_Float16, (uint16_t)Sl.swa[j]);
-        const _Float16 swb = __builtin_bit_cast(_Float16, (uint16_t)Sl.swb[j]);
+  for (int e = 0; e < C::NH; e++) h[e] = 0.0f;
+
+  // One phase's part of the chain: thread e of the phase's EPS (over all
+  // wavefronts, a different start per phase) walks the blocks of chunk c.
+  auto h_thread = [&](int k) { return ((wave - k * C::EPS / 64) & (DW - 1)) * 64 + lane; };
+  auto h_rank = [&](int k, int e) {   // rank of thread e's element in phase k
+    const int bt = e / C::EPT;
+    return (bt / (C::PT > 0 ? C::PT : 1) * HT + k * C::PT + bt % (C::PT > 0 ? C::PT : 1)) * 16 + e % C::EPT / MX;
+  };
+  auto chain = [&](int k, int buf, int c, float &hv) {
+    int e = h_thread(k);
+    asm volatile("" : "+v"(e));   // its addresses are formed here, not kept over the K loop
+    if (e < C::EPS) {
+      const float *P = reinterpret_cast<const float *>(smem + LY.p + buf * C::PBUF) +
+                       (C::TR ? e * C::PS : e / C::EPT * GL * C::EPT + e % C::EPT);
+      const uint16_t *sl = reinterpret_cast<const uint16_t *>(smem + LY.sl + (LY.nb == 2 ? (c & 1) * sl_buf : 0)) +
+                           (C::TR ? h_rank(k, e) * C::SLS : h_rank(k, e));
+      const int rs = geo.r_pad32;
+      float t = hv;
+      // NG groups' products (128-wide groups: a group's two blocks' products
+      // with s_x add exactly, |I| < 2^13, into its one step) and scales, in
+      // batches of B
+      auto walk = [&](auto NGC, auto GKC) {
+        constexpr int NG = decltype(NGC)::value, GK = decltype(GKC)::value, B = NG < 8 ? NG : 8;
 #pragma unroll
-        for (int v = 0; v < 4; v++) {
-          acc[j][v] = fmaf(I1[v] * sxa[v], (float)swa, acc[j][v]);
-          acc[j][v] = fmaf(I2[v] * sxb[v], (float)swb, acc[j][v]);
+        for (int g0 = 0; g0 < NG; g0 += B) {
+          if (g0 > 0 && c * NG + g0 >= KQ) break;   // the rest of the last chunk adds zeros
+          float p8[B];
+          _Float16 s8[B];
+          if constexpr (C::TR) {
+            const u32x4 w = *reinterpret_cast<const u32x4 *>(sl + g0);
+#pragma unroll
+            for (int i = 0; i < B; i++) s8[i] = half_of(w[i / 2], i & 1);
+#pragma unroll
+            for (int i = 0; i < B * GK / 4; i++) {
+              const v4f w4 = *reinterpret_cast<const v4f *>(P + g0 * GK + 4 * i);
+              if constexpr (GK == 1) {
+#pragma unroll
+                for (int j = 0; j < 4; j++) p8[4 * i + j] = w4[j];
+              } else {
+                p8[2 * i] = w4[0] + w4[1];
+                p8[2 * i + 1] = w4[2] + w4[3];
+              }
+            }
+          } else {
+#pragma unroll
+            for (int i = 0; i < B; i++) {
+              s8[i] = half_of(sl[(g0 + i) * rs], 0);
+              const float *pg = P + (g0 + i) * GK * C::PG;
+              p8[i] = GK == 1 ? pg[0] : pg[0] + pg[C::PG];
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < B; i++) t = fmaf(p8[i], (float)s8[i], t);
+          if (!C::TR) __builtin_amdgcn_sched_barrier(0);   // a batch at a time: registers
         }
-      }
+      };
+      if (gk == 1) walk(std::integral_constant<int, GL>{}, std::integral_constant<int, 1>{});
+      else walk(std::integral_constant<int, GL / 2>{}, std::integral_constant<int, 2>{});
+      hv = t;
     }
   };
 
-  // The two roles keep their rings in separate scopes, so their registers
-  // overlap.  Each issues its first loads, then joins the prologue's barrier.
-  if (s1) {
-    S1Slot S1[D1];
-#pragma unroll
-    for (int s = 0; s < D1; s++) load_s1(S1[s], min(s, NP - 1));
-    prologue();
-    // slot s holds pair i0 + s; it is refilled after pair i's chain step
-    S1Lds lds2 = s1_lds(min(1, NP - 1));
-    S1Prod prod = s1_mfma(s1_lds(0), S1[0]);
-    auto s1_step = [&](int i, int s) {
-      const S1Lds lds_next = s1_lds(min(i + 2, NP - 1));
-      const S1Prod prod_next = s1_mfma(lds2, S1[(s + 1) % D1]);
-      s1_chain(prod, S1[s]);
-      prod = prod_next;
-      lds2 = lds_next;
+  // ---- K loop ----
+  // the chain's few wavefronts (up to two tokens) end last: theirs go first
+  if (HT > 0 && MODE <= 2 && wave * 64 < C::EPS) __builtin_amdgcn_s_setprio(2);
+  int phase = 0;
+  auto chunk = [&](int c, Slot &Q) {
+    const int p = c * PCH + pl;   // this wavefront's pair
+    const v8i av = act_op(p);
+    const Sx sx = xs_row(2 * p + gq);
+    auto h_tile = [&](int j, int pt, float *P) {
+      const v8i b = unpack32(Q.b[j]);
+      load_tile(Q, j);
+      float *D = C::TR ? P + ((hsub * C::PT + pt) * C::EPT + c16 * MX) * C::PS + 2 * pl
+                       : P + ((hsub * C::PT + pt) * GL + 2 * pl) * C::EPT + c16 * MX;
+      // (one and two tokens: rows 4-7 repeat rows 0-3, so lanes 16-31 and 48-63
+      // write their neighbours' values to the same place)
+      const v4f t = times_sx(mfma_codes_16x16x128(av, b), sx);
+      if constexpr (MODE == 1) {
+        D[gq] = t[0];
+      } else if constexpr (MODE == 2) {
+        D[gq] = t[0];
+        D[gq + C::PS] = t[1];
+      } else {
+        *reinterpret_cast<v4f *>(D + gq * C::EPT + 4 * qh) = t;
+      }
     };
-    int i0 = 0;
-    if constexpr (MV <= 2) {
-      // whole rounds of the ring with no per-pair test, so that the
-      // pipeline's registers rotate by renaming inside a round (a per-pair
-      // test splits the round into blocks joined by register copies), then
-      // the last NP % D1 pairs.  (With four rows per lane the longer-lived
-      // operands do not fit 128 registers that way: those layouts keep the
-      // tested loop.)
-      for (; i0 + D1 <= NP; i0 += D1) {
+    auto residual = [&]() {
 #pragma unroll
-        for (int s = 0; s < D1; s++) {
-          s1_step(i0 + s, s);
-          load_s1(S1[s], min(i0 + s + D1, NP - 1));
+      for (int j = 0; j < CW; j++) {
+        if (MODE > 2) __builtin_amdgcn_sched_barrier(0);
+        const v8i b = unpack32(Q.b[HT + j]);
+        load_tile(Q, HT + j);
+        const v4f t = times_sx(mfma_codes_16x16x128(av, b), sx);
+        const float sw = (float)half_of(Q.sw[j], 0);
+#pragma unroll
+        for (int v = 0; v < MV; v++) acc[j][v] = fmaf(t[v], sw, acc[j][v]);
+      }
+    };
+    if constexpr (HT == 0) {
+      residual();
+      load_scales(Q);
+    } else {
+#pragma unroll
+      for (int k = 0; k < C::NPHASE; k++, phase++) {
+        const int buf = LY.nb == 2 ? phase & 1 : 0;
+        // the chain of the phase before (its products are behind the last
+        // barrier), ahead of this phase's products: its few wavefronts wait on
+        // LDS and on their own fmas while the others multiply; with one buffer
+        // it must end before the products are overwritten
+        const int kp = k > 0 ? k - 1 : C::NPHASE - 1;
+        if (phase > 0) {
+          chain(kp, LY.nb == 2 ? buf ^ 1 : 0, k > 0 ? c : c - 1, h[kp * C::EPS / (64 * DW)]);
+          if (LY.nb == 1) d_barrier();
         }
+        float *P = reinterpret_cast<float *>(smem + LY.p + buf * C::PBUF);
+#pragma unroll
+        for (int pt = 0; pt < C::PT; pt++) h_tile(k * C::PT + pt, pt, P);
+        if (MODE > 2) __builtin_amdgcn_sched_barrier(0);   // (more operands at once would not fit the registers)
+        if (k == 0) {
+          sl_write(c);
+          sl_load();
+          residual();
+        }
+        if (k == C::NPHASE - 1) load_scales(Q);
+        d_barrier();
       }
     }
-    for (; i0 < NP; i0 += D1) {
+  };
+  for (int c = 0; c < NCH; c += C::PD) {
 #pragma unroll
-      for (int s = 0; s < D1; s++) {
-        if (i0 + s < NP) s1_step(i0 + s, s);
-        load_s1(S1[s], min(i0 + s + D1, NP - 1));
-      }
-    }
-  } else {
-    ResSlot<CTW> SR[D2];
-    const int plast = nres_it > 0 ? ph + (nres_it - 1) * NPH : 0;
-#pragma unroll
-    for (int s = 0; s < D2; s++) load_res(SR[s], min(ph + s * NPH, plast));
-    prologue();
-    for (int i0 = 0; i0 < nres_it; i0 += D2) {
-#pragma unroll
-      for (int s = 0; s < D2; s++) {
-        const int i = i0 + s;
-        if (i < nres_it) residual(SR[s], ph + i * NPH);
-        load_res(SR[s], min(ph + (i + D2) * NPH, plast));
-      }
-    }
+    for (int u = 0; u < C::PD; u++)
+      if (C::PD == 1 || c + u < NCH) chunk(c + u, ring[u]);
   }
-  __syncthreads();   // every wavefront is done with the activation codes
+  if constexpr (HT > 0)
+    chain(C::NPHASE - 1, LY.nb == 2 ? (phase - 1) & 1 : 0, NCH - 1, h[(C::NPHASE - 1) * C::EPS / (64 * DW)]);
+  __builtin_amdgcn_s_setprio(0);
+  d_barrier();   // every wavefront is done with the K loop's LDS
 
   // ---- epilogue: residual partials, H, re-quantization, stage 2, store ----
-  float *RES = reinterpret_cast<float *>(smem + LY.epi_res);   // [NPH][CT][16 tokens][16 columns]
-  float *HS = reinterpret_cast<float *>(smem + LY.epi_h);      // [16][HSTR]
-  uint8_t *QS = smem + LY.epi_q;                                // [16][QSTR] fp8 codes
-  float *SHS = reinterpret_cast<float *>(smem + LY.epi_sh);    // [2][16]
-  constexpr int HSTR = DLayout::HSTR, QSTR = DLayout::QSTR;
-  const bool store_lane = !MD::TOK8 || lane < 32;
-  if (rbusy) {
+  float *RES = reinterpret_cast<float *>(smem);                // [PCH][CT][8 tokens][16 columns]
+  float *HS = reinterpret_cast<float *>(smem + C::E_H);        // [16][HSTR]
+  uint8_t *QS = smem + C::E_Q;                                  // [16][QSTR] fp8 codes
+  float *SHS = reinterpret_cast<float *>(smem + C::E_SH);      // [2][16]
+  constexpr int HSTR = C::HSTR, QSTR = C::QSTR;
 #pragma unroll
-    for (int j = 0; j < CTW; j++)
-#pragma unroll
-      for (int v = 0; v < MV; v++) {
-        float val = acc[j][v];
-        if constexpr (MD::TOK8) val += upper_half(val);   // group A + group B partials
-        const int t = MD::TOK8 ? 4 * qh + v : 4 * q + v;
-        if (store_lane) RES[((ph * CT + tg * CTW + j) * 16 + t) * 16 + c16] = val;
-      }
-  }
-  if (s1) {
+  for (int j = 0; j < CW; j++)
 #pragma unroll
     for (int v = 0; v < MV; v++) {
-      const int t = MD::TOK8 ? 4 * qh + v : 4 * q + v;
-      if (store_lane) HS[t * HSTR + 16 * wave + c16] = hacc[v];
+      const float val = acc[j][v] + upper_half(acc[j][v]);   // block A + block B partials
+      const int t = 4 * qh + v;
+      if (lane < 32 && (S == 1 || sub * CW + j < CT)) RES[((pl * CT + sub * CW + j) * 8 + t) * 16 + c16] = val;
     }
-  }
-  const int RB = (r + 63) / 64;   // 64-rank blocks of stage 2 (<= 2)
-  if (r > 0) {
+  if constexpr (HT > 0) {
+#pragma unroll
+    for (int k = 0; k < C::NPHASE; k++) {
+      const int e = h_thread(k);
+      if (e < C::EPS) HS[e % MX * HSTR + h_rank(k, e)] = h[k * C::EPS / (64 * DW)];
+    }
     for (int idx = tid; idx < 16 * RB * 64; idx += 64 * DW) {
       const int row = idx / (RB * 64), j = idx % (RB * 64);
       if (j >= r) QS[row * QSTR + j] = 0;
     }
   }
-  __syncthreads();
+  d_barrier();
 
-  if (r > 0) {
+  if constexpr (HT > 0) {
     // Re-quantize H per token and rank group (s_H stays fp32).  Half a
     // wavefront per token row (wavefront w < 8: rows 2w, 2w + 1); lane j of
     // the half takes ranks epl j .. epl j + epl - 1, so a rank group is a run
@@ -577,7 +691,7 @@ __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
       const int hg = j / lpg;
       const bool valid = j * epl < r;
       const bool live = valid && row < m;
-      const bool dbg = a.dbg_h != nullptr && blockIdx.x == 0;
+      const bool dbg = a.dbg_h != nullptr && cblk == 0;
       float hv[4];
       float amax = 0.0f;
 #pragma unroll
@@ -600,8 +714,8 @@ __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
             }
             w |= code_to_fp8(qv) << (8 * e);
             if (dbg && row < m) {
-              a.dbg_h[(int64_t)row * r + j * epl + e] = hv[e];
-              a.dbg_qh[(int64_t)row * r + j * epl + e] = (int8_t)qv;
+              a.dbg_h[(int64_t)(m0 + row) * r + j * epl + e] = hv[e];
+              a.dbg_qh[(int64_t)(m0 + row) * r + j * epl + e] = (int8_t)qv;
             }
           }
         }
@@ -611,30 +725,24 @@ __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
         else *qd = (uint8_t)w;
         if (j % lpg == 0) {
           SHS[hg * 16 + row] = sh;
-          if (dbg && row < m) a.dbg_sh[(int64_t)row * rg + hg] = sh;
+          if (dbg && row < m) a.dbg_sh[(int64_t)(m0 + row) * rg + hg] = sh;
         }
       }
     }
-    __syncthreads();
+    d_barrier();
   }
 
   // ---- stage 2 and the single epilogue: wavefront j < CT stores tile j ----
+  const v8i z8 = {0, 0, 0, 0, 0, 0, 0, 0};
   if (wave < CT) {
     const int j = wave;
     const int ct = c0 + j;
     if (ct < ct16) {
       v4f ylr = v4f{0, 0, 0, 0};
       const int orow0 = 4 * q;   // output rows 4q .. 4q + 3 of this lane
-      if (r > 0) {
-        const int rbq = min(q >> 1, RB - 1);
-        const int L = qh * 32 + (ct & 1) * 16 + c16;
-        const u32x4 l2raw = *reinterpret_cast<const u32x4 *>(
-            l2codes + (((int64_t)(ct >> 1) * (geo.r_pad64 / 64) + rbq) * 64 + L) * 16);
-        const int col = ct * 16 + c16;
-        const float s2a = half_bits_to_float(l2scales[col]);
-        const int hg1 = 64 / geo.gr;   // rank group of the second 64-rank block (0 if gr = 128)
-        const float s2b = RB > 1 ? half_bits_to_float(l2scales[(int64_t)hg1 * geo.n_pad + col]) : 0.0f;
-        const v8i qa = lds_v8i(QS + c16 * QSTR + rbq * 64 + qh * 32);
+      if constexpr (HT > 0) {
+        const float s2a = half_bits_to_float((uint16_t)l2sa), s2b = half_bits_to_float((uint16_t)l2sb);
+        const v8i qa = lds_v8i(QS + c16 * QSTR + min(gq, RB - 1) * 64 + qh * 32);
         const v8i lb = unpack32(l2raw);
         {
           const v4f cb = mfma_codes_16x16x128(q < 2 ? qa : z8, lb);
@@ -657,10 +765,11 @@ __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
           const int row = orow0 + v;
           if (row < m) {
             float yres = 0.0f;
-            for (int w2 = 0; w2 < NPH; w2++) yres += RES[((w2 * CT + j) * 16 + row) * 16 + c16];
+#pragma unroll
+            for (int w2 = 0; w2 < PCH; w2++) yres += RES[((w2 * CT + j) * 8 + row) * 16 + c16];
             const float yv = yres + ylr[v];
             const uint16_t bits = a.bf16_out ? float_to_bf16_bits(yv) : float_to_half_bits(yv);
-            reinterpret_cast<uint16_t *>(a.y)[(int64_t)row * geo.n + col] = bits;
+            reinterpret_cast<uint16_t *>(a.y)[(int64_t)(m0 + row) * geo.n + col] = bits;
           }
         }
       }
@@ -668,56 +777,64 @@ __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
   }
 }
 
-template <int MODE, int CT, bool FQ>
+template <int MODE, int R, int CT>
 hipError_t launch_decode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
-  const DLayout LY = decode_layout<MODE, CT>(a.geo.k / kGroup, a.geo.r);
+  using C = DCfg<MODE, R, CT>;
+  const DLayout LY = DLayout::make<C>(a.geo.k / kGroup, a.geo.r_pad32);
   const int tiles16 = a.geo.n_pad / 16;
   if (a.geo.gk != 1 && a.geo.gk != 2) return hipErrorInvalidValue;
-  // the group width is a compile-time constant where the registers allow it
-  // (64-wide groups up to two rows per lane, 128-wide groups at one row): the
-  // chain then takes one or two steps per pair without a per-pair choice
-  constexpr int MV = DMode<MODE>::MV;
-  auto kern = a.geo.gk == 1 ? dual_gemm_decode_kernel<MODE, CT, FQ, MV <= 2 ? 1 : 0>
-                            : dual_gemm_decode_kernel<MODE, CT, FQ, MV == 1 ? 2 : 0>;
+  auto kern = dual_gemm_decode_kernel<MODE, R, CT>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, LY.total);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((tiles16 + CT - 1) / CT), dim3(64 * DW), LY.total, s, a, xh);
+  hipLaunchKernelGGL(kern, dim3((tiles16 + CT - 1) / CT * ((a.m + 7) / 8)), dim3(64 * DW), LY.total, s, a, xh);
   return hipGetLastError();
 }
 
-template <int MODE, bool FQ>
+template <int MODE, int R>
+hipError_t launch_decode_r(int ct, const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
+  switch (ct) {
+    case 1: return launch_decode<MODE, R, 1>(a, xh, s);
+    case 2: return launch_decode<MODE, R, 2>(a, xh, s);
+    case 4: return launch_decode<MODE, R, 4>(a, xh, s);
+    case 8: return launch_decode<MODE, R, 8>(a, xh, s);
+    default: return launch_decode<MODE, R, 16>(a, xh, s);
+  }
+}
+
+template <int MODE>
 hipError_t launch_decode_mode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
   // the fewest 16-column tiles per work-group that keep the grid within one
   // work-group per CU
-  const int tiles16 = a.geo.n_pad / 16;
-  if (tiles16 <= 256) return launch_decode<MODE, 1, FQ>(a, xh, s);
-  if (tiles16 <= 512) return launch_decode<MODE, 2, FQ>(a, xh, s);
-  if (tiles16 <= 1024) return launch_decode<MODE, 4, FQ>(a, xh, s);
-  return launch_decode<MODE, 8, FQ>(a, xh, s);
+  const int tiles16 = a.geo.n_pad / 16 * ((a.m + 7) / 8);
+  const int ct = tiles16 <= 256 ? 1 : (tiles16 <= 512 ? 2 : (tiles16 <= 1024 ? 4 : (tiles16 <= 2048 ? 8 : 16)));
+  switch (rank_tiles(a.geo.r)) {
+    case 0: return launch_decode_r<MODE, 0>(ct, a, xh, s);
+    case 1: return launch_decode_r<MODE, 1>(ct, a, xh, s);
+    case 2: return launch_decode_r<MODE, 2>(ct, a, xh, s);
+    case 4: return launch_decode_r<MODE, 4>(ct, a, xh, s);
+    case 8: return launch_decode_r<MODE, 8>(ct, a, xh, s);
+    default: return hipErrorInvalidValue;
+  }
 }
-
-int decode_mode(int m) { return m == 1 ? 1 : (m == 2 ? 2 : (m <= 8 ? 4 : 16)); }
 
 }  // namespace
 
+// K for which the decode kernel takes m tokens: 112 KiB of codes, as fp8 bytes
+// for one or two tokens, 4-bit for 8 or (two token blocks, each with its own)
+// 16
 bool decode_fits(int m, int k) {
   if (m < 1 || m > kDecodeMaxTokens) return false;
-  const int mode = decode_mode(m);
-  const int mx = mode == 16 ? 16 : (mode <= 2 ? mode : 8);
-  const int xb = mode <= 2 ? 64 : 32;
+  const int bytes = m <= 2 ? m * 64 : (m <= 8 ? 8 : 16) * 32;   // per 64-wide block
   const int64_t kgp = (int64_t)(k / kGroup + 1) / 2 * 2;
-  return kgp * mx * xb <= kDecodeXBytes;
+  return kgp * bytes <= kDecodeXBytes;
 }
 
+// xh: fp16 activations to quantize in the kernel, or NULL: codes from a.xc / a.xs
 hipError_t launch_dual_gemm_decode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
-  const bool fq = xh != nullptr;
-  switch (decode_mode(a.m)) {
-    case 1: return fq ? launch_decode_mode<1, true>(a, xh, s) : launch_decode_mode<1, false>(a, xh, s);
-    case 2: return fq ? launch_decode_mode<2, true>(a, xh, s) : launch_decode_mode<2, false>(a, xh, s);
-    case 4: return fq ? launch_decode_mode<4, true>(a, xh, s) : launch_decode_mode<4, false>(a, xh, s);
-    default: return fq ? launch_decode_mode<16, true>(a, xh, s) : launch_decode_mode<16, false>(a, xh, s);
-  }
+  if (a.m == 1) return launch_decode_mode<1>(a, xh, s);
+  if (a.m == 2) return launch_decode_mode<2>(a, xh, s);
+  return launch_decode_mode<4>(a, xh, s);
 }
 
 }  // namespace tq

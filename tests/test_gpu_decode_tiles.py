@@ -1,0 +1,40 @@
+"""GPU parity of the decode kernel's wide work-groups (sixteen column tiles,
+four wavefronts per pair of K blocks) and of its two token blocks."""
+import numpy as np
+import pytest
+
+import paper_2606_01556_amd as tq
+from test_gpu_parity import full_parity, run_gpu, say
+from tq_synth import random_codes_layer
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    tq.lib()
+    yield
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("M,K,N,r,group", [
+    (1, 192, 33000, 128, 64),      # one token, an odd number of K blocks
+    (2, 1280, 32800, 16, 128),     # one rank tile, formed by all four wavefronts of a pair
+    (5, 640, 32784, 32, 64),       # two rank tiles, each formed twice; a ragged last tile
+    (9, 1088, 16500, 64, 64),      # a second token block of one token
+    (16, 512, 16400, 128, 128),
+    (12, 320, 20000, 0, 64),
+])
+def test_wide_work_groups(oracle_mod, M, K, N, r, group):
+    """More column tiles (times token blocks) than eight per CU: codes and fp16
+    activations in, the same bits out of both, H bit-exact."""
+    say(f"decode wide M={M} K={K} N={N} r={r} group={group}")
+    d = random_codes_layer(M, K, N, r, seed=M + N + r)
+    args = (d["X"], d["W_res"], d["L1"], d["L2"])
+    g, _ = full_parity(oracle_mod, *args, group=group)
+    assert g["kernel"] == "decode"
+    g2 = run_gpu(*args, debug=False, fused_quant=True, group=group)
+    np.testing.assert_array_equal(g["Ybits"], g2["Ybits"])
