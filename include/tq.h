@@ -160,6 +160,19 @@ tq_status tq_dual_gemm(const tq_weight_desc *d, const void *packed, const void *
 tq_status tq_dual_gemm_fused_quant(const tq_weight_desc *d, const void *packed, const void *x,
                                    int m, void *y, tq_dtype y_dtype, void *stream);
 
+/* The whole layer from fp16 activations x [m,k], row-major: the activation
+ * quantizer, then the fused layer -- one launch (tq_dual_gemm_fused_quant) for
+ * few tokens, else tq_quant_act and tq_dual_gemm one after the other, with the
+ * codes and scales in `scratch`.  The results are the same bits either way.
+ *   scratch  device buffer of tq_layer_scratch_bytes(d, m) bytes, 16-byte
+ *            aligned, owned by the caller and free again when the stream has
+ *            run the call; may be NULL where that size is 0
+ * m == 0 is a no-op.  Errors as tq_quant_act and tq_dual_gemm (TQ_ERR_NULL for a
+ * NULL scratch that is needed). */
+size_t tq_layer_scratch_bytes(const tq_weight_desc *d, int m);
+tq_status tq_layer(const tq_weight_desc *d, const void *packed, const void *x, int m, void *y,
+                   tq_dtype y_dtype, void *scratch, void *stream);
+
 /* Kernels of tq_dual_gemm. */
 typedef enum {
   TQ_KERNEL_DECODE = 0,   /* m <= 16: weight-streaming, H formed in every work-group */

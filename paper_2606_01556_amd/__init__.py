@@ -9,6 +9,7 @@ itself and has no CPU fallback: if the library is missing it raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import numpy as np
@@ -43,7 +44,8 @@ EXPORTS = ("tq_weight_desc_init", "tq_pack_weights", "tq_quant_act", "tq_dual_ge
            "tq_dual_gemm_fused_quant", "tq_dual_gemm_debug", "tq_export_weights",
            "tq_act_codes_bytes", "tq_unfused_scratch_bytes", "tq_dual_gemm_unfused",
            "tq_dual_gemm_unfused_noalloc", "tq_dual_gemm_kernel", "tq_status_string",
-           "tq_export_weights_canonical", "tq_act_codes_canonical")
+           "tq_export_weights_canonical", "tq_act_codes_canonical", "tq_layer",
+           "tq_layer_scratch_bytes")
 
 _lib = None
 
@@ -72,13 +74,16 @@ def lib() -> ctypes.CDLL:
         L.tq_unfused_scratch_bytes.restype = ctypes.c_size_t
         L.tq_dual_gemm_unfused.argtypes = [D, P, P, P, I, P, I, P, P]
         L.tq_dual_gemm_unfused_noalloc.argtypes = [D, P, P, P, I, P, I, P]
+        L.tq_layer.argtypes = [D, P, P, I, P, I, P, P]
+        L.tq_layer_scratch_bytes.argtypes = [D, I]
+        L.tq_layer_scratch_bytes.restype = ctypes.c_size_t
         L.tq_export_weights.argtypes = [D, P, P, P, P, P, P, P, P]
         L.tq_export_weights_canonical.argtypes = [D, P, P, P, P, P, P, P, P]
         L.tq_act_codes_canonical.argtypes = [P, P, I, I, I, P, P, P]
         L.tq_status_string.argtypes = [I]
         L.tq_status_string.restype = ctypes.c_char_p
         for name in EXPORTS:
-            if name not in ("tq_act_codes_bytes", "tq_unfused_scratch_bytes",
+            if name not in ("tq_act_codes_bytes", "tq_unfused_scratch_bytes", "tq_layer_scratch_bytes",
                             "tq_dual_gemm_kernel", "tq_status_string"):
                 getattr(L, name).restype = I
         _lib = L
@@ -99,10 +104,23 @@ def _ptr(t):
     return t.data_ptr()
 
 
+_raw_stream = None
+
+
+def _current_stream():
+    """The current stream's hipStream_t, without building a torch.cuda.Stream."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()      # initialises CUDA
+        get_device, get_raw = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+        _raw_stream = lambda: get_raw(get_device())
+    return _raw_stream()
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -344,9 +362,17 @@ def dual_gemm_kernel(desc: WeightDesc, m: int) -> str:
     return KERNEL_NAMES[k]
 
 
+@functools.lru_cache(maxsize=256)
 def act_codes_bytes(m: int, k: int) -> int:
     """Bytes of the x_codes buffer of m tokens (tq_act_codes_bytes)."""
     return int(lib().tq_act_codes_bytes(m, k))
+
+
+@functools.lru_cache(maxsize=256)
+def layer_scratch_bytes(m: int, k: int, group: int = GROUP) -> int:
+    """Bytes of tq_layer's scratch where it takes two launches: the codes (rounded
+    up to 256 bytes) and the scales of m tokens."""
+    return (act_codes_bytes(m, k) + 255) // 256 * 256 + padded_tokens(m) * (k // group) * 2
 
 
 def empty_act(m: int, k: int, device="cuda", group: int = GROUP):
@@ -377,18 +403,30 @@ class Layer:
         pack_weights(self.desc, w_res.contiguous(), None if l1 is None else l1.contiguous(),
                      None if l2 is None else l2.contiguous(), self.packed, stream)
         self.n, self.k, self.rank = n, k, r
+        # up to this many tokens the layer is one launch and needs no scratch
+        self._one_launch = 0
+        while self._one_launch < 16 and not lib().tq_layer_scratch_bytes(self.desc, self._one_launch + 1):
+            self._one_launch += 1
 
     def __call__(self, x, bf16: bool = False, stream=None):
-        """Y = layer(x) for fp16 x [m, k]: tq_quant_act, then tq_dual_gemm."""
+        """Y = layer(x) for fp16 x [m, k] (tq_layer: the activation quantizer and
+        the fused layer)."""
         import torch
         _tensor(x, "x", torch.float16)
         if x.dim() != 2 or x.shape[1] != self.k:
             raise ValueError(f"x: expected [m, {self.k}], got shape {tuple(x.shape)}")
         m = x.shape[0]
-        xc, xs = empty_act(m, self.k, x.device, self.desc.group)
-        y = torch.empty((m, self.n), dtype=torch.bfloat16 if bf16 else torch.float16, device=x.device)
-        quant_act(x, xc, xs, self.desc.group, stream=stream)
-        dual_gemm(self.desc, self.packed, xc, xs, m, y, bf16, stream)
+        y = x.new_empty((m, self.n), dtype=torch.bfloat16 if bf16 else None)
+        scratch = None
+        if m > self._one_launch:
+            scratch = x.new_empty((layer_scratch_bytes(m, self.k, self.desc.group) // 2,))
+        st = _stream(stream)
+        _check(lib().tq_layer(self.desc, self.packed.data_ptr(), x.data_ptr(), m, y.data_ptr(),
+                              TQ_BF16 if bf16 else TQ_F16, None if scratch is None else scratch.data_ptr(), st),
+               "tq_layer")
+        if stream is not None and scratch is not None and st != _current_stream():
+            # freed here, in use there: its memory waits for that stream
+            scratch.record_stream(torch.cuda.ExternalStream(st, device=x.device))
         return y
 
 

@@ -784,8 +784,7 @@ hipError_t launch_decode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
   const int tiles16 = a.geo.n_pad / 16;
   if (a.geo.gk != 1 && a.geo.gk != 2) return hipErrorInvalidValue;
   auto kern = dual_gemm_decode_kernel<MODE, R, CT>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, LY.total);
+  hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), LY.total);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((tiles16 + CT - 1) / CT * ((a.m + 7) / 8)), dim3(64 * DW), LY.total, s, a, xh);
   return hipGetLastError();

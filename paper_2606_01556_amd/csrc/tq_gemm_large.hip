@@ -483,8 +483,7 @@ hipError_t launch_large(const GemmArgs &a, hipStream_t s) {
   const int n_tiles = (a.geo.n_pad + LBN - 1) / LBN;
   const int band = m_tiles < 8 ? m_tiles : 8;   // token blocks per band of the XCD order
   auto kern = dual_gemm_large_kernel<RT, GK>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+  hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), C::LDS);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(m_tiles * n_tiles), dim3(64 * LW), C::LDS, s, a, m_tiles, n_tiles,
                      band);

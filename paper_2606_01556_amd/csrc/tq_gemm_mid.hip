@@ -541,8 +541,7 @@ hipError_t launch_mid(const GemmArgs &a, hipStream_t s) {
   const int n_rb = (a.ms / 32 + TB - 1) / TB;
   const int n_cb = (a.geo.n_pad / 32 + CT - 1) / CT;
   auto kern = dual_gemm_mid_kernel<TB, RT, CT, GK, FP8>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+  hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), C::LDS);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(n_rb * n_cb), dim3(64 * MW), C::LDS, s, a, n_rb);
   return hipGetLastError();

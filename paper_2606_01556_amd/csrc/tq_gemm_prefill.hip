@@ -786,8 +786,7 @@ hipError_t launch_prefill(const GemmArgs &a, hipStream_t s) {
   const int n_chunks = (n_tiles + cpw - 1) / cpw;
   const int band = m_tiles < 8 ? m_tiles : 8;   // token blocks per band of the XCD order
   auto kern = dual_gemm_prefill_kernel<RT, D, GK>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+  hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), C::LDS);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(m_tiles * n_chunks), dim3(64 * PNW), C::LDS, s, a, m_tiles,
                      n_tiles, n_chunks, cpw, band);

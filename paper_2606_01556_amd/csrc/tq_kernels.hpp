@@ -53,6 +53,12 @@ struct GemmArgs {
   int mid_ct;           // 0: the mid kernel's plan of least time; else 1, 2 or 4 column tiles (tests)
 };
 
+// Lets `kern` use `bytes` of dynamic LDS (more than 64 KiB must be asked for).
+inline hipError_t allow_lds(const void *kern, int bytes) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
 // gk: 64-wide K blocks per quantization group (1 or 2)
 hipError_t launch_quant_act(const uint16_t *x, int m, int k, int gk, uint32_t *codes,
                             uint16_t *scales, hipStream_t s);

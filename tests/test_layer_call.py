@@ -1,0 +1,70 @@
+"""The whole-layer entry (tq_layer) and Layer.__call__: argument checks and
+scratch sizes on the CPU, the same bits as the quantizer and the fused layer
+called one after the other on the GPU."""
+import copy
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2606_01556_amd as tq
+from tq_synth import random_codes_layer
+
+torch = pytest.importorskip("torch")
+FAKE = 1 << 20     # 16-byte aligned fake device address; never dereferenced
+
+
+def test_scratch_sizes():
+    """0 where the layer is one launch (few tokens, and few values for every
+    work-group to quantize), else the binding's own formula."""
+    L = tq.lib()
+    for n, k, r, g in ((512, 512, 16, 64), (4096, 4096, 64, 64), (4096, 14336, 64, 128), (256, 28672, 128, 64),
+                       (64, 131072, 0, 128)):
+        d = tq.weight_desc_init(n, k, r, g)
+        for m in (1, 2, 7, 8, 9, 16, 17, 512, 513, 1000):
+            got = L.tq_layer_scratch_bytes(d, m)
+            one = m <= 16 and (m == 1 or min(m, 8) * k <= 32768) and k <= 114688
+            assert got == (0 if one else tq.layer_scratch_bytes(m, k, g)), (k, m)
+    assert L.tq_layer_scratch_bytes(d, 0) == 0 and L.tq_layer_scratch_bytes(tq.WeightDesc(), 100) == 0
+
+
+def test_validation():
+    L = tq.lib()
+    d = tq.weight_desc_init(128, 4096, 64)
+    call = lambda dd=d, p=FAKE, x=FAKE, m=100, y=FAKE, t=0, s=FAKE: L.tq_layer(dd, p, x, m, y, t, s, None)
+    assert call(dd=None) == 1 and call(p=None) == 1 and call(x=None) == 1 and call(y=None) == 1
+    assert call(s=None) == 1                        # two launches need scratch
+    assert call(dd=tq.WeightDesc()) == 7
+    assert call(m=-1) == 2 and call(m=65535 * 32 + 1) == 2
+    assert call(t=5) == 5 and call(t=5, m=1) == 5
+    assert call(x=FAKE + 8) == 6 and call(s=FAKE + 8) == 6 and call(y=FAKE + 2, m=1) == 6
+    assert call(m=0) == 0
+    assert ctypes.sizeof(tq.WeightDesc) > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n,r,group,bf16", [
+    (1, 4096, 300, 64, 64, False), (8, 4096, 300, 64, 64, True), (8, 4160, 300, 64, 64, False),
+    (16, 512, 96, 16, 128, False), (16, 4160, 96, 16, 64, True), (17, 256, 100, 0, 64, False),
+    (513, 256, 100, 32, 64, False),
+])
+def test_layer_call(m, k, n, r, group, bf16):
+    """Either side of the one-launch rule, of the 4-bit / fp8 code formats, and
+    on another stream than the current one."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("[case]", m, k, n, r, group, bf16, flush=True)
+    d = random_codes_layer(m, k, n, r, seed=m + k)
+    dev = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    lay = tq.Layer(dev(d["W_res"]), dev(d["L1"]), dev(d["L2"]), group=group)
+    x = dev(d["X"])
+    xc, xs = tq.empty_act(m, k, group=group)
+    tq.quant_act(x, xc, xs, group)
+    ref = torch.empty((m, n), dtype=torch.bfloat16 if bf16 else torch.float16, device="cuda")
+    tq.dual_gemm(lay.desc, lay.packed, xc, xs, m, ref, bf16)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for layer, stream in ((lay, None), (lay, side), (copy.deepcopy(lay), None)):
+        y = layer(x, bf16, stream=stream)
+        torch.cuda.synchronize()
+        assert y.dtype == ref.dtype and torch.equal(y.view(torch.int16), ref.view(torch.int16))
