@@ -286,18 +286,24 @@ struct PKernel {
     return o;
   }
 
-  __device__ __forceinline__ static void read_raw(const uint8_t *S, const RawOff &o, Raw &R) {
-    const uint8_t *pa = S + o.a, *pb = S + o.b, *psa = S + o.sa, *psb = S + o.sb;
+  __device__ __forceinline__ static void read_a(const uint8_t *S, const RawOff &o, Raw &R) {
+    const uint8_t *pa = S + o.a;
 #pragma unroll
-    for (int i = 0; i < 2; i++) {
+    for (int i = 0; i < 2; i++)
       R.a[i] = join(*reinterpret_cast<const u32x4 *>(pa + i * 2048),
                     *reinterpret_cast<const u32x4 *>(pa + i * 2048 + 1024));
-      R.sa[i] = *reinterpret_cast<const uint16_t *>(psa + i * 64);
-    }
+  }
+  __device__ __forceinline__ static void read_b(const uint8_t *S, const RawOff &o, Raw &R) {
+    const uint8_t *pb = S + o.b;
 #pragma unroll
-    for (int j = 0; j < 2; j++) {
-      R.b[j] = *reinterpret_cast<const u32x4 *>(pb + j * 1024);
-      R.sb[j] = *reinterpret_cast<const uint16_t *>(psb + j * 64);
+    for (int j = 0; j < 2; j++) R.b[j] = *reinterpret_cast<const u32x4 *>(pb + j * 1024);
+  }
+  __device__ __forceinline__ static void read_s(const uint8_t *S, const RawOff &o, Raw &R) {
+    const uint8_t *psa = S + o.sa, *psb = S + o.sb;
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      R.sa[i] = *reinterpret_cast<const uint16_t *>(psa + i * 64);
+      R.sb[i] = *reinterpret_cast<const uint16_t *>(psb + i * 64);
     }
   }
 
@@ -308,15 +314,16 @@ struct PKernel {
   //         of tiles 00, 01, 10, 11), with this wavefront's loads of a later
   //         group interleaved between them (their scalar address arithmetic
   //         issues while the matrix core works);
-  //   Y(g): the LDS reads of group g + 1, the 64 rescaling fmas of group g (on
-  //         products that X(g) has finished) and the expansion of the weight
-  //         operands of group g + 1.
+  //   Y(g): the LDS reads of group g + 1 (64-wide groups: without the weight
+  //         codes, read in X(g)), the 64 rescaling fmas of group g (on products
+  //         that X(g) has finished) and the expansion of the weight operands of
+  //         group g + 1.
   // Every wavefront runs X(0) Y(0) X(1) Y(1) ... with one workgroup barrier per
   // group, placed after X(g) on wavefronts 0-3 (GA) and after Y(g) on
   // wavefronts 4-7 (each SIMD holds one of each), so between barriers k - 1 and
   // k wavefront A runs Y(k - 1) X(k) while wavefront B runs X(k) Y(k).
   //
-  // Ring hand-over.  In that interval A reads group k and B group k + 1, so
+  // Ring hand-over.  In that interval A reads groups k and k + 1 and B group k + 1, so
   // the barrier that opens it must publish groups <= k + 1; slot s is free
   // once both readers of its group have passed the barrier after their reads.
   // Each wavefront issues its loads of group k + D - 1 into slot (k - 1) % D
@@ -325,6 +332,17 @@ struct PKernel {
   // (D - 3 groups), so groups <= k + 2 are complete when barrier k opens.  The
   // prologue loads groups 0 .. D - 2; loads past the last group repeat the
   // last group into a free slot.
+  // The order of X: the four code products, then the four short scale products,
+  // so the products Y waits for last are the short ones.  With 64-wide groups
+  // the next group's weight codes are read from LDS at X's start (their raw
+  // registers are free since the last expansion), which shortens Y; with
+  // 128-wide groups X is the longer phase and that read stays in Y.  Both
+  // phases X run above the vector phases' priority, B's above A's: B's X opens
+  // the interval and its Y ends it, so B is the later one at the barrier.
+  // Measured with K = 8192, N = 28672, r = 128, M = 4096, us per call: 1155 ->
+  // 1130 with 64-wide groups, 1013 -> 951 with 128-wide ones; the scale products
+  // interleaved with the code products, one priority for both, and the
+  // expansion moved between the products (1196 with 64-wide groups) are slower.
   // (THREE: this wavefront also loads the scales, three loads per group; a
   // template parameter, so that the loop body is one basic block)
   //
@@ -350,7 +368,9 @@ struct PKernel {
     __syncthreads();
     const RawOff ro = raw_off(lane, wr, wc);
     Raw R;
-    read_raw(smem, ro, R);
+    read_a(smem, ro, R);
+    read_b(smem, ro, R);
+    read_s(smem, ro, R);
     wait_lgkm0();
     v8i b0 = unpack32(R.b[0]), b1 = unpack32(R.b[1]);
     auto hand_over = [&]() {
@@ -371,7 +391,9 @@ struct PKernel {
     // the last block: the last block again, never used); X(g)'s loads: this
     // wavefront's share of block g + D - 1 into the slot that block g - 1 left
     auto y_reads = [&](int g) {
-      read_raw(smem + rd_off, ro, R);
+      read_a(smem + rd_off, ro, R);
+      if (GK == 2) read_b(smem + rd_off, ro, R);
+      read_s(smem + rd_off, ro, R);
       const uint32_t nx = rd_off + C::STAGE == (uint32_t)C::RING ? 0u : rd_off + C::STAGE;
       rd_off = g + 2 < KG ? nx : rd_off;
       asm volatile("" ::: "memory");
@@ -391,7 +413,7 @@ struct PKernel {
       if constexpr (GK == 2) {
         // ---- X(g): the group's first block, held ----
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(1);
+        __builtin_amdgcn_s_setprio(GA ? 1 : 2);
         c00 = codes_half(R.a[0], b0);
         c01 = codes_half(R.a[0], b1);
         c10 = codes_half(R.a[1], b0);
@@ -419,30 +441,22 @@ struct PKernel {
       const int gb = g + GK - 1;   // the group's last block
       // ---- X(gb) ----
       __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(1);
+      __builtin_amdgcn_s_setprio(GA ? 1 : 2);
+      if (GK == 1) read_b(smem + rd_off, ro, R);   // the raw weight registers are free since Y(g - 1)
       if constexpr (GK == 2) {
         c00 = codes_half_acc(R.a[0], b0, c00);
-      } else {
-        c00 = codes_half(R.a[0], b0);
-      }
-      const v16f p00 = outer2(R.sa[0], R.sb[0]);
-      if constexpr (GK == 2) {
         c01 = codes_half_acc(R.a[0], b1, c01);
-      } else {
-        c01 = codes_half(R.a[0], b1);
-      }
-      const v16f p01 = outer2(R.sa[0], R.sb[1]);
-      if constexpr (GK == 2) {
         c10 = codes_half_acc(R.a[1], b0, c10);
-      } else {
-        c10 = codes_half(R.a[1], b0);
-      }
-      const v16f p10 = outer2(R.sa[1], R.sb[0]);
-      if constexpr (GK == 2) {
         c11 = codes_half_acc(R.a[1], b1, c11);
       } else {
+        c00 = codes_half(R.a[0], b0);
+        c01 = codes_half(R.a[0], b1);
+        c10 = codes_half(R.a[1], b0);
         c11 = codes_half(R.a[1], b1);
       }
+      const v16f p00 = outer2(R.sa[0], R.sb[0]);
+      const v16f p01 = outer2(R.sa[0], R.sb[1]);
+      const v16f p10 = outer2(R.sa[1], R.sb[0]);
       const v16f p11 = outer2(R.sa[1], R.sb[1]);
       x_loads(gb);
       // one product, then a few of the loads' scalar, memory and address
