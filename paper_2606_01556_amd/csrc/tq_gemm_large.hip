@@ -457,22 +457,10 @@ __global__ __launch_bounds__(64 * LW, 1) void dual_gemm_large_kernel(GemmArgs a,
           ylr[v] = fmaf(cbv[v], SHS[hg * LBM + 32 * ti + row_of_32x32(lane, v)] * sl2, ylr[v]);
       }
     }
-    // the matrix-core products above read operands from every lane: keep
-    // them out of the per-lane store branch below
-    asm volatile("" : "+v"(ylr));
     const v16f &acc = j == 0 ? acc0 : acc1;
-    const int col = ct * 32 + l32;
-    if (ct < ct32 && col < geo.n) {
 #pragma unroll
-      for (int v = 0; v < 16; v++) {
-        const int row = m0 + 32 * ti + row_of_32x32(lane, v);
-        if (row < m) {
-          const float yv = acc[v] + ylr[v];
-          const uint16_t bits = a.bf16_out ? float_to_bf16_bits(yv) : float_to_half_bits(yv);
-          reinterpret_cast<uint16_t *>(a.y)[(int64_t)row * geo.n + col] = bits;
-        }
-      }
-    }
+    for (int v = 0; v < 16; v++) ylr[v] += acc[v];
+    store_tile_32x32(a.y, a.bf16_out, m, geo.n, m0 + 32 * ti, ct * 32, lane, ylr);
   }
 }
 

@@ -506,9 +506,6 @@ __global__ __launch_bounds__(64 * MW, 2) void dual_gemm_mid_kernel(GemmArgs a, i
             ylr[v] = fmaf(cbv[v], SHS[hg * C::ROWS + 32 * t + row_of_32x32(lane, v)] * sl2, ylr[v]);
         }
       }
-      // the matrix-core products above read operands from every lane: keep
-      // them out of the per-lane store branch below
-      asm volatile("" : "+v"(ylr));
       v16f yres = acc[t];
 #pragma unroll
       for (int p = 0; p < C::NPH - 1; p++) {
@@ -519,18 +516,9 @@ __global__ __launch_bounds__(64 * MW, 2) void dual_gemm_mid_kernel(GemmArgs a, i
           yres[v] += r4[0]; yres[v + 1] += r4[1]; yres[v + 2] += r4[2]; yres[v + 3] += r4[3];
         }
       }
-      const int col = ct * 32 + l32;
-      if (col < geo.n) {
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-          const int row = C::ROWS * tb + 32 * t + row_of_32x32(lane, v);
-          if (row < m) {
-            const float yv = yres[v] + ylr[v];
-            const uint16_t bits = a.bf16_out ? float_to_bf16_bits(yv) : float_to_half_bits(yv);
-            reinterpret_cast<uint16_t *>(a.y)[(int64_t)row * geo.n + col] = bits;
-          }
-        }
-      }
+      for (int v = 0; v < 16; v++) yres[v] += ylr[v];
+      store_tile_32x32(a.y, a.bf16_out, m, geo.n, C::ROWS * tb + 32 * t, ct * 32, lane, yres);
     }
   }
 }

@@ -725,7 +725,6 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
 #pragma unroll
       for (int j = 0; j < 2; j++) {
         const int ct = n0 / 32 + 2 * wc + j;
-        const bool cvalid = ct < ctiles;
         v16f ylr = v16f{0};
         if constexpr (RT > 0) {
           const uint8_t *QS = smem + C::OFF_Q;
@@ -764,21 +763,9 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
             }
           }
         }
-        // the matrix-core products above read operands from every lane: keep
-        // them out of the per-lane store branch below
-        asm volatile("" : "+v"(ylr));
-        const int col = ct * 32 + l32e;
-        if (cvalid && col < geo.n) {
 #pragma unroll
-          for (int v = 0; v < 16; v++) {
-            const int row = m0_e + 32 * ti + row_of_32x32(lane_e, v);
-            if (row < m) {
-              const float yv = acc[i][j][v] + ylr[v];
-              const uint16_t bits = a.bf16_out ? float_to_bf16_bits(yv) : float_to_half_bits(yv);
-              reinterpret_cast<uint16_t *>(a.y)[(int64_t)row * geo.n + col] = bits;
-            }
-          }
-        }
+        for (int v = 0; v < 16; v++) ylr[v] += acc[i][j][v];
+        store_tile_32x32(a.y, a.bf16_out, m, geo.n, m0_e + 32 * ti, ct * 32, lane_e, ylr);
       }
     }
     wait_vm<0>();      // stores drained before the next block's loads are counted
