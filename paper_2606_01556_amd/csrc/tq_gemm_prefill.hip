@@ -271,35 +271,53 @@ struct PKernel {
     uint32_t sa[2], sb[2];
   };
 
-  // This lane's byte offsets within a slot (loop-invariant): one address add
-  // per operand kind and group, the rest are immediate offsets.
+  // Operand addresses within a slot: a wave-uniform part u and a lane part l
+  // per operand kind.  With 64-wide groups the loop fills all 256 registers, and
+  // a spill reload in it waits for every load in flight: the uniform parts stay
+  // scalar and two lane parts serve all four kinds.  With 128-wide groups there
+  // is room, and one register per kind saves the scalar adds (4096 -> 14336
+  // r = 128, M = 4096: 269 against 284 us).
+  template <int GK>
   struct RawOff {
-    uint32_t a, b, sa, sb;
+    uint32_t ua = 0, ub = 0, usa = 0, usb = 0, la, lb, lsa, lsb;
+    __device__ __forceinline__ RawOff(int lane, int wr, int wc) {
+      ua = P_A + 2 * wr * 2048;
+      ub = P_B + 2 * wc * 1024;
+      usa = P_SX + 64 * wr * 2;
+      usb = P_SW + 64 * wc * 2;
+      la = lb = lane * 16;
+      lsa = lsb = (lane & 31) * 2;
+      if (GK == 2) {
+        la += ua; lb += ub; lsa += usa; lsb += usb;
+        ua = ub = usa = usb = 0;
+      }
+    }
   };
-  __device__ __forceinline__ static RawOff raw_off(int lane, int wr, int wc) {
-    const int l32 = lane & 31;
-    RawOff o;
-    o.a = P_A + 2 * wr * 2048 + lane * 16;
-    o.b = P_B + 2 * wc * 1024 + lane * 16;
-    o.sa = P_SX + (64 * wr + l32) * 2;
-    o.sb = P_SW + (64 * wc + l32) * 2;
-    return o;
+  template <int GK>
+  __device__ __forceinline__ static const uint8_t *at(const uint8_t *smem, uint32_t u, uint32_t l) {
+    if (GK == 1) asm("" : "+s"(u));   // the lane part is added last
+    return smem + u + l;
   }
-
-  __device__ __forceinline__ static void read_a(const uint8_t *S, const RawOff &o, Raw &R) {
-    const uint8_t *pa = S + o.a;
+  template <int GK>
+  __device__ __forceinline__ static void read_a(const uint8_t *smem, uint32_t slot, const RawOff<GK> &o,
+                                                Raw &R) {
+    const uint8_t *pa = at<GK>(smem, slot + o.ua, o.la);
 #pragma unroll
     for (int i = 0; i < 2; i++)
       R.a[i] = join(*reinterpret_cast<const u32x4 *>(pa + i * 2048),
                     *reinterpret_cast<const u32x4 *>(pa + i * 2048 + 1024));
   }
-  __device__ __forceinline__ static void read_b(const uint8_t *S, const RawOff &o, Raw &R) {
-    const uint8_t *pb = S + o.b;
+  template <int GK>
+  __device__ __forceinline__ static void read_b(const uint8_t *smem, uint32_t slot, const RawOff<GK> &o,
+                                                Raw &R) {
+    const uint8_t *pb = at<GK>(smem, slot + o.ub, o.lb);
 #pragma unroll
     for (int j = 0; j < 2; j++) R.b[j] = *reinterpret_cast<const u32x4 *>(pb + j * 1024);
   }
-  __device__ __forceinline__ static void read_s(const uint8_t *S, const RawOff &o, Raw &R) {
-    const uint8_t *psa = S + o.sa, *psb = S + o.sb;
+  template <int GK>
+  __device__ __forceinline__ static void read_s(const uint8_t *smem, uint32_t slot, const RawOff<GK> &o,
+                                                Raw &R) {
+    const uint8_t *psa = at<GK>(smem, slot + o.usa, o.lsa), *psb = at<GK>(smem, slot + o.usb, o.lsb);
 #pragma unroll
     for (int i = 0; i < 2; i++) {
       R.sa[i] = *reinterpret_cast<const uint16_t *>(psa + i * 64);
@@ -353,24 +371,20 @@ struct PKernel {
   // integer sum of the whole group) and issues the group's four scale
   // products; only the second block's Y applies fmas.  Every wait and barrier
   // is the same per block as for 64-wide groups.
-  template <bool GA, bool THREE, int GK, typename Pre>
+  template <bool GA, bool THREE, int GK>
   __device__ __forceinline__ static void main_loop_pp(const PPlan &P, uint8_t *smem,
                                                       uint32_t ring_lds, int KG, int lane, int wr,
-                                                      int wc, v16f (&acc)[2][2], Pre pre) {
+                                                      int wc, v16f (&acc)[2][2]) {
     static_assert(D >= 4, "the hand-over keeps D - 3 groups of loads in flight");
     static_assert(GK == 1 || GK == 2, "64- or 128-wide quantization groups");
     constexpr int L = THREE ? 3 : 2;   // loads per block
-    wait_vm<0>();
-    pre();
-#pragma unroll
-    for (int s = 0; s < D - 1; s++) p_issue<GK>(P, THREE, min(s, KG - 1), ring_lds + s * C::STAGE);
     wait_vm<L * (D - 3)>();
     __syncthreads();
-    const RawOff ro = raw_off(lane, wr, wc);
+    const RawOff<GK> ro(lane, wr, wc);
     Raw R;
-    read_a(smem, ro, R);
-    read_b(smem, ro, R);
-    read_s(smem, ro, R);
+    read_a(smem, 0, ro, R);
+    read_b(smem, 0, ro, R);
+    read_s(smem, 0, ro, R);
     wait_lgkm0();
     v8i b0 = unpack32(R.b[0]), b1 = unpack32(R.b[1]);
     auto hand_over = [&]() {
@@ -391,9 +405,9 @@ struct PKernel {
     // the last block: the last block again, never used); X(g)'s loads: this
     // wavefront's share of block g + D - 1 into the slot that block g - 1 left
     auto y_reads = [&](int g) {
-      read_a(smem + rd_off, ro, R);
-      if (GK == 2) read_b(smem + rd_off, ro, R);
-      read_s(smem + rd_off, ro, R);
+      read_a(smem, rd_off, ro, R);
+      if (GK == 2) read_b(smem, rd_off, ro, R);
+      read_s(smem, rd_off, ro, R);
       const uint32_t nx = rd_off + C::STAGE == (uint32_t)C::RING ? 0u : rd_off + C::STAGE;
       rd_off = g + 2 < KG ? nx : rd_off;
       asm volatile("" ::: "memory");
@@ -442,7 +456,7 @@ struct PKernel {
       // ---- X(gb) ----
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(GA ? 1 : 2);
-      if (GK == 1) read_b(smem + rd_off, ro, R);   // the raw weight registers are free since Y(g - 1)
+      if (GK == 1) read_b(smem, rd_off, ro, R);   // the raw weight registers are free since Y(g - 1)
       if constexpr (GK == 2) {
         c00 = codes_half_acc(R.a[0], b0, c00);
         c01 = codes_half_acc(R.a[0], b1, c01);
@@ -494,6 +508,12 @@ struct PKernel {
   // block per ring slot and step; a 128-wide group (GK = 2) adds its second
   // block's code products to its first's in the matrix core before its one
   // scale product.
+  // Block s + 1's LDS reads are issued ahead of block s's products.
+  struct HRaw {
+    v8i a;
+    u32x4 l[C::HT];
+    uint32_t sa, sl[C::HT];
+  };
   template <int GK>
   __device__ __forceinline__ static void h_loop(const HPlan &P, uint8_t *smem, uint32_t ring_lds,
                                                 int KG, int lane, bool hw, int ti,
@@ -504,40 +524,43 @@ struct PKernel {
     wait_vm<2 * (D - 1)>();
     __syncthreads();
     const int l32 = lane & 31;
-    for (int s0 = 0; s0 < KG; s0 += GK) {
+    auto read = [&](int s, HRaw &q) {
+      const uint8_t *S = smem + (s % D) * C::STAGE;
+      q.a = join(*reinterpret_cast<const u32x4 *>(S + P_A + ti * 2048 + lane * 16),
+                 *reinterpret_cast<const u32x4 *>(S + P_A + ti * 2048 + 1024 + lane * 16));
+      q.sa = *reinterpret_cast<const uint16_t *>(S + H_S + (32 * ti + l32) * 2);
+#pragma unroll
+      for (int h = 0; h < C::HT; h++) {
+        q.l[h] = *reinterpret_cast<const u32x4 *>(S + P_B + 1024 * hrt[h] + lane * 16);
+        q.sl[h] = *reinterpret_cast<const uint16_t *>(S + H_S + 256 + (32 * hrt[h] + l32) * 2);
+      }
+    };
+    HRaw q[2];
+    if (hw) read(0, q[0]);
+    // two blocks per pass, so that the two register sets alternate without moves
+    for (int s0 = 0; s0 < KG; s0 += 2) {
       v16f hc[C::HT];
 #pragma unroll
-      for (int u = 0; u < GK; u++) {
+      for (int u = 0; u < 2; u++) {
         const int s = s0 + u;
-        const uint8_t *S = smem + (s % D) * C::STAGE;
-        v8i ra = v8i{0};
-        u32x4 rl[C::HT];
-        uint32_t sa = 0, sl[C::HT];
-        if (hw) {
-          ra = join(*reinterpret_cast<const u32x4 *>(S + P_A + ti * 2048 + lane * 16),
-                    *reinterpret_cast<const u32x4 *>(S + P_A + ti * 2048 + 1024 + lane * 16));
-          sa = *reinterpret_cast<const uint16_t *>(S + H_S + (32 * ti + l32) * 2);
+        if (GK == 2 || s < KG) {
+          // block s + 1 has landed and every wavefront is done with slot s
+          wait_vm<2 * (D - 2)>();
+          wait_lgkm0();
+          __syncthreads();
+          h_issue(P, min(s + D, KG - 1), ring_lds + (s % D) * C::STAGE);
+          if (hw) {
+            read(s + 1, q[1 - u]);   // past the last block: a repeat of it, never used
 #pragma unroll
-          for (int h = 0; h < C::HT; h++) {
-            rl[h] = *reinterpret_cast<const u32x4 *>(S + P_B + 1024 * hrt[h] + lane * 16);
-            sl[h] = *reinterpret_cast<const uint16_t *>(S + H_S + 256 + (32 * hrt[h] + l32) * 2);
-          }
-        }
-        // block s + 1 has landed and every wavefront is done with slot s
-        wait_vm<2 * (D - 2)>();
-        wait_lgkm0();
-        __syncthreads();
-        h_issue(P, min(s + D, KG - 1), ring_lds + (s % D) * C::STAGE);
-        if (hw) {
-#pragma unroll
-          for (int h = 0; h < C::HT; h++) {
-            const v8i lb = unpack32(rl[h]);
-            if (u == 0) {
-              hc[h] = codes_half(ra, lb);
-            } else {
-              hc[h] = codes_half_acc(ra, lb, hc[h]);
+            for (int h = 0; h < C::HT; h++) {
+              const v8i lb = unpack32(q[u].l[h]);
+              if (GK == 1 || u == 0) {
+                hc[h] = codes_half(q[u].a, lb);
+              } else {
+                hc[h] = codes_half_acc(q[u].a, lb, hc[h]);
+              }
+              if (GK == 1 || u == 1) fma16(hacc[h], hc[h], outer2(q[u].sa, q[u].sl[h]));
             }
-            if (u == GK - 1) fma16(hacc[h], hc[h], outer2(sa, sl[h]));
           }
         }
       }
@@ -595,6 +618,18 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
 
   const uint8_t *l2codes = a.packed + geo.off_l2;
   const uint16_t *l2scales = reinterpret_cast<const uint16_t *>(a.packed + geo.off_l2s);
+
+  // The first D - 1 groups of a column block into the ring: for every block but
+  // a run's first this is done ahead of the previous block's epilogue, whose
+  // arithmetic and stores cover the latency (with the H pass's early reads
+  // 4096 -> 14336, M = 4096: r = 128, 128-wide groups 278 -> 270 us; r = 64,
+  // 64-wide groups 316 -> 306 us).
+  auto fill = [&](int n0) {
+    PPlan P;
+    plan_main(a, lane, wave, m0, n0, P);
+#pragma unroll
+    for (int s = 0; s < D - 1; s++) p_issue<GK>(P, wave == 0, min(s, KG - 1), ring_lds + s * C::STAGE);
+  };
 
   for (int cb = cb_begin; cb < cb_end; cb++) {
     const int n0 = cb * PBN;
@@ -678,6 +713,7 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
     }
 
     // ---- residual 4-bit GEMM of the block ----
+    if (cb == cb_begin) fill(n0);
     PPlan P;
     plan_main(a, lane, wave, m0, n0, P);
     v16f acc[2][2];
@@ -689,29 +725,30 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
     // and scales) travel with the first groups of the K loop, loaded by the
     // wavefront with wr = 0 (published by the K loop's first barrier)
     const uint32_t l2_lds = ring_lds + C::OFF_L2 + wc * C::L2W;
-    auto pre = [&]() {
-      if (RT > 0 && wr == 0) {
+    if (RT > 0 && wr == 0) {
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
-          const int ct = min(n0 / 32 + 2 * wc + j, ctiles - 1);
+      for (int j = 0; j < 2; j++) {
+        const int ct = min(n0 / 32 + 2 * wc + j, ctiles - 1);
 #pragma unroll
-          for (int rbk = 0; rbk < C::RB; rbk++)
-            dma_s(lane * 16, uniform_ptr(l2codes + ((int64_t)ct * C::RB + rbk) * 1024),
-                  l2_lds + (j * C::RB + rbk) * 1024);
-        }
-        // lane q < 8 RG: 8 scales of column tile j = q / (4 RG), rank group
-        // (q / 4) % RG, columns 8 (q % 4) .. + 8
-        const int q = lane & (8 * RG - 1);
-        const int jj = q / (4 * RG), hg = (q / 4) % RG;
-        const int ct = min(n0 / 32 + 2 * wc + jj, ctiles - 1);
-        dma_v(reinterpret_cast<const uint8_t *>(l2scales + (int64_t)hg * geo.n_pad + ct * 32 +
-                                                8 * (q & 3)),
-              l2_lds + 2 * C::RB * 1024);
+        for (int rbk = 0; rbk < C::RB; rbk++)
+          dma_s(lane * 16, uniform_ptr(l2codes + ((int64_t)ct * C::RB + rbk) * 1024),
+                l2_lds + (j * C::RB + rbk) * 1024);
       }
-    };
-    if (wave == 0) K::template main_loop_pp<true, true, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc, pre);
-    else if (wr == 0) K::template main_loop_pp<true, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc, pre);
-    else K::template main_loop_pp<false, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc, pre);
+      // lane q < 8 RG: 8 scales of column tile j = q / (4 RG), rank group
+      // (q / 4) % RG, columns 8 (q % 4) .. + 8
+      const int q = lane & (8 * RG - 1);
+      const int jj = q / (4 * RG), hg = (q / 4) % RG;
+      const int ct = min(n0 / 32 + 2 * wc + jj, ctiles - 1);
+      dma_v(reinterpret_cast<const uint8_t *>(l2scales + (int64_t)hg * geo.n_pad + ct * 32 +
+                                              8 * (q & 3)),
+            l2_lds + 2 * C::RB * 1024);
+    }
+    if (wave == 0) K::template main_loop_pp<true, true, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc);
+    else if (wr == 0) K::template main_loop_pp<true, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc);
+    else K::template main_loop_pp<false, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc);
+
+    __syncthreads();   // every wavefront is done with the ring
+    if (cb + 1 < cb_end) fill(n0 + PBN);
 
     // ---- stage 2 (Q_H Q(L2)) and the single epilogue ----
     // (the index values are re-derived here, behind an opaque copy, so the
@@ -768,8 +805,8 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
         store_tile_32x32(a.y, a.bf16_out, m, geo.n, m0_e + 32 * ti, ct * 32, lane_e, ylr);
       }
     }
-    wait_vm<0>();      // stores drained before the next block's loads are counted
-    __syncthreads();   // the next block refills the ring
+    wait_vm<0>();      // the next block's first groups have landed, the stores are drained
+    __syncthreads();   // the next block reloads the stage-2 operands
   }
 }
 
