@@ -723,7 +723,7 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
       for (int j = 0; j < 2; j++) acc[i][j] = v16f{0};
     // the stage-2 operands of this column pair's two column tiles (L2 blocks
     // and scales) travel with the first groups of the K loop, loaded by the
-    // wavefront with wr = 0 (published by the K loop's first barrier)
+    // wavefront with wr = 0, behind the fill's
     const uint32_t l2_lds = ring_lds + C::OFF_L2 + wc * C::L2W;
     if (RT > 0 && wr == 0) {
 #pragma unroll
@@ -747,6 +747,9 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
     else if (wr == 0) K::template main_loop_pp<true, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc);
     else K::template main_loop_pp<false, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc);
 
+    // The stage-2 operands have landed once D - 3 blocks' loads behind them are
+    // all that a hand-over leaves in flight, at block D - 4; a shorter K waits here.
+    if (KG < D - 3) wait_vm<0>();
     __syncthreads();   // every wavefront is done with the ring
     if (cb + 1 < cb_end) fill(n0 + PBN);
 

@@ -62,3 +62,19 @@ def test_stores_end_at_the_tile(m, k, n, r, group, bf16):
         # than the largest |Y| times the terms that add to it
         tol = want.abs() * 2.0 ** (-7 if bf16 else -10) + want.abs().max() * k * 2.0 ** -24
         assert ((y - want).abs() <= tol).all()
+
+
+@pytest.mark.parametrize("k,r,group", [(64, 128, 64), (192, 128, 64), (64, 64, 64), (256, 64, 64),
+                                       (128, 128, 128), (256, 64, 128)])
+def test_prefill_short_k(k, r, group):
+    """K loops shorter than the prefill kernel's ring, over a run of three column
+    blocks (more token blocks than CUs): stage 2's operands are loaded behind the
+    ring's first fill and have to have landed by the epilogue."""
+    m, n = 257 * 128 - 5, 600
+    print(f"prefill short k={k} r={r} group={group}", flush=True)
+    gen = torch.Generator("cuda").manual_seed(k + r)
+    draw = lambda *s: torch.randn(*s, generator=gen, device="cuda").half()
+    layer = tq.Layer(draw(n, k), draw(k, r), draw(r, n), group=group)
+    x = draw(m, k)
+    y, want = store(layer, x, "prefill", False), store(layer, x, "large", False)
+    assert torch.equal(y.view(torch.int16), want.view(torch.int16))
