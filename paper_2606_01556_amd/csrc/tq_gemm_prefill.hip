@@ -747,9 +747,10 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
     else if (wr == 0) K::template main_loop_pp<true, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc);
     else K::template main_loop_pp<false, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc);
 
-    // The stage-2 operands have landed once D - 3 blocks' loads behind them are
-    // all that a hand-over leaves in flight, at block D - 4; a shorter K waits here.
-    if (KG < D - 3) wait_vm<0>();
+    // Each block's loads (two or more) are behind the stage-2 operands, so all but
+    // the last two landing covers those also for the shortest K.  No test of K: a
+    // branch here cost 2 % at 8192 -> 28672, r = 128, M = 8192.
+    wait_vm<2>();
     __syncthreads();   // every wavefront is done with the ring
     if (cb + 1 < cb_end) fill(n0 + PBN);
 
