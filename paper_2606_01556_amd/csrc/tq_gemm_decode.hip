@@ -10,9 +10,10 @@
 // first reader leaves it) in addition to its columns.
 //  * K is cut into pairs of 64-wide blocks, and a wavefront takes whole pairs:
 //    it reads the pair's activation operand once and multiplies it with the
-//    pair's operands of every rank tile and every column tile (or, with S = 2,
-//    with its half of the tiles).  So all sixteen wavefronts carry the same
-//    work whatever the rank, and the activation operand is shared by all tiles.
+//    pair's operands of every rank tile and every column tile (or S of them
+//    share a pair, each with its part of the tiles).  So all sixteen wavefronts
+//    carry the same work whatever the rank, and the activation operand is shared
+//    by all tiles of a wavefront.
 //  * The residual sums stay in the wavefront's registers; the partial sums of
 //    the wavefronts are added in a fixed order at the end (the order of Y's
 //    fp32 accumulation is free; H's is not).
@@ -80,21 +81,34 @@ struct DMode {
   static constexpr int PTM = 8 / MODE;
 };
 
+// R rank tiles and CT column tiles of a work-group.  S wavefronts share a pair,
+// each with its part of the tiles.
+constexpr int split_hs(int r, int s) { return r == 0 || r > s ? s : r; }   // of these, with rank tiles of their own (the others repeat them)
+constexpr int split_ht(int r, int s) { return r / split_hs(r, s); }        // rank tiles of a wavefront
+constexpr int split_cw(int ct, int s) { return ct > s ? ct / s : 1; }      // column tiles (fewer than S: kept by the first)
+// The fewest wavefronts whose operands and sums fit their 128 registers (one
+// token, eight column tiles, r = 32 in one wavefront spilled 24: 8192 -> 28672
+// 28.9 us, 22.9 with two), or that are ever the fastest (the last line); and the
+// most that still divide the tiles.
+constexpr int split_min(int mode, int r, int ct) {
+  if (ct == 16 || (mode > 2 && r >= 4 && r + ct > 10)) return 4;
+  if (r + ct > (mode == 1 ? 10 : (mode == 2 ? 8 : 5)) || ct == 8) return 2;
+  return mode > 2 && r == 4 ? 2 : 1;
+}
+constexpr int split_max(int mode, int r, int ct) {
+  const int tiles = r > ct ? r : ct, s = ct == 16 ? 8 : (tiles < 4 ? tiles : 4);
+  return s > split_min(mode, r, ct) ? s : split_min(mode, r, ct);
+}
+
 // LDS layout (bytes).  K loop: the activation codes, their fp16 scales, NB
 // buffers of H products [rank tile][block][16 ranks][MX tokens] fp32, and NB of
 // L1 scales [group of the chunk][rank] fp16.  Epilogue, from the start: the
 // residual partials, H, Q_H and s_H.
-// R rank tiles and CT column tiles of a work-group.  S wavefronts share a pair
-// (each with its part of the tiles) where one would hold more operands and sums
-// than its 128 registers take.
-template <int MODE, int R, int CT>
+template <int MODE, int R, int CT, int S_>
 struct DCfg {
   using MD = DMode<MODE>;
-  static constexpr int S = CT == 16 || (MODE > 2 && R >= 4 && R + CT > 10) ? 4
-                           : (R + CT > (MODE == 1 ? 10 : (MODE == 2 ? 8 : 5)) ? 2 : 1);
-  static constexpr int HS = R == 0 || R > S ? S : R;     // of these, with rank tiles of their own (the others repeat them)
-  static constexpr int HT = R / HS;                      // rank tiles of a wavefront
-  static constexpr int CW = CT > S ? CT / S : 1;         // column tiles (fewer than S: kept by the first)
+  static constexpr int S = S_;
+  static constexpr int HS = split_hs(R, S), HT = split_ht(R, S), CW = split_cw(CT, S);
   static constexpr bool H = HT > 0;
   static constexpr int PCH = DW / S;                     // pairs of a chunk
   static constexpr int GL = 2 * PCH;                     // 64-wide blocks of a chunk
@@ -109,7 +123,7 @@ struct DCfg {
   // meet in a bank), else [block][element]; L1 scales [rank][row] or [row][rank]
   static constexpr bool TR = MODE <= 2;
   static constexpr int PS = TR ? GL + 4 : 1, PG = TR ? 1 : EPT;   // element and block strides, floats
-  static constexpr int SLS = GL + 8;                     // rank stride of the transposed scales
+  static constexpr int SLS = GL < 8 ? 16 : GL + 8;        // rank stride of the transposed scales
   static constexpr int PBUF = PT * HS * EPT * (TR ? PS : GL) * 4;
   static constexpr int NH = HT && NPHASE * EPS > 64 * DW ? NPHASE * EPS / (64 * DW) : 1;   // per thread
   static constexpr int HSTR = kMaxRank + 1;              // fp32 per H row
@@ -204,13 +218,13 @@ __device__ __forceinline__ uint32_t d_load2(__amdgpu_buffer_rsrc_t rsrc, uint32_
   return __builtin_amdgcn_raw_buffer_load_b16(rsrc, off, 0, 0);
 }
 
-template <int MODE, int R, int CT>
+template <int MODE, int R, int CT, int S>
 __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
                                                                    const uint16_t *__restrict__ xh) {
-  using C = DCfg<MODE, R, CT>;
+  using C = DCfg<MODE, R, CT, S>;
   using MD = DMode<MODE>;
   constexpr int MX = MD::MX, MV = MD::MV, XB = MD::XB, PCH = C::PCH, GL = C::GL;
-  constexpr int S = C::S, HT = C::HT, CW = C::CW;
+  constexpr int HT = C::HT, CW = C::CW;
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const Geometry &geo = a.geo;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -777,27 +791,62 @@ __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
   }
 }
 
-template <int MODE, int R, int CT>
+template <int MODE, int R, int CT, int S>
 hipError_t launch_decode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
-  using C = DCfg<MODE, R, CT>;
+  using C = DCfg<MODE, R, CT, S>;
   const DLayout LY = DLayout::make<C>(a.geo.k / kGroup, a.geo.r_pad32);
   const int tiles16 = a.geo.n_pad / 16;
   if (a.geo.gk != 1 && a.geo.gk != 2) return hipErrorInvalidValue;
-  auto kern = dual_gemm_decode_kernel<MODE, R, CT>;
+  auto kern = dual_gemm_decode_kernel<MODE, R, CT, S>;
   hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), LY.total);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((tiles16 + CT - 1) / CT * ((a.m + 7) / 8)), dim3(64 * DW), LY.total, s, a, xh);
   return hipGetLastError();
 }
 
+// Wavefronts per pair.  A chunk takes a wavefront its tiles' time (a rank tile
+// 0.7 of a column tile, which has scales of its own) and about one tile's more
+// for the barrier and the chain; filling the first chunk and the epilogue take
+// about 1.5 times the tiles.  So a K of few pairs, whose only chunk would leave
+// most wavefronts without one, is split wide (512 -> 4096 r = 128, one token:
+// four per pair 6.7 us, one 8.4), and one that fills whole chunks as little as
+// the registers allow (28672 -> 8192 r = 128: one per pair 39 us, two 41, four
+// 52).  A wider split has to be 4 % cheaper: its chunks are shorter, which
+// costs 3 to 5 % where the weights come from HBM.  The choice is within 5 % of
+// the fastest at 98 % of 2200 calls timed (K 512 to 28672, N 512 to 28672, r 0
+// to 128, both group widths).
+constexpr int split_cost(int r, int ct, int s, int pairs) {
+  const int pch = DW / s, chunks = (pairs + pch - 1) / pch;
+  const int tiles = 7 * split_ht(r, s) + 10 * split_cw(ct, s);
+  return 2 * chunks * (tiles + 10) + 3 * tiles;
+}
+
+template <int MODE, int R, int CT, int S>
+hipError_t launch_decode_s(int split, const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
+  if constexpr (S < split_max(MODE, R, CT)) {
+    if (split > S) return launch_decode_s<MODE, R, CT, 2 * S>(split, a, xh, s);
+  }
+  return launch_decode<MODE, R, CT, S>(a, xh, s);
+}
+
+template <int MODE, int R, int CT>
+hipError_t launch_decode_ct(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
+  constexpr int lo = split_min(MODE, R, CT), hi = split_max(MODE, R, CT);
+  const int pairs = (a.geo.k / kGroup + 1) / 2;
+  int split = lo;
+  for (int c = 2 * lo; c <= hi; c *= 2)
+    if (25 * split_cost(R, CT, c, pairs) < 24 * split_cost(R, CT, split, pairs)) split = c;
+  return launch_decode_s<MODE, R, CT, lo>(split, a, xh, s);
+}
+
 template <int MODE, int R>
 hipError_t launch_decode_r(int ct, const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
   switch (ct) {
-    case 1: return launch_decode<MODE, R, 1>(a, xh, s);
-    case 2: return launch_decode<MODE, R, 2>(a, xh, s);
-    case 4: return launch_decode<MODE, R, 4>(a, xh, s);
-    case 8: return launch_decode<MODE, R, 8>(a, xh, s);
-    default: return launch_decode<MODE, R, 16>(a, xh, s);
+    case 1: return launch_decode_ct<MODE, R, 1>(a, xh, s);
+    case 2: return launch_decode_ct<MODE, R, 2>(a, xh, s);
+    case 4: return launch_decode_ct<MODE, R, 4>(a, xh, s);
+    case 8: return launch_decode_ct<MODE, R, 8>(a, xh, s);
+    default: return launch_decode_ct<MODE, R, 16>(a, xh, s);
   }
 }
 

@@ -38,3 +38,33 @@ def test_wide_work_groups(oracle_mod, M, K, N, r, group):
     assert g["kernel"] == "decode"
     g2 = run_gpu(*args, debug=False, fused_quant=True, group=group)
     np.testing.assert_array_equal(g["Ybits"], g2["Ybits"])
+
+
+@pytest.mark.parametrize("M,K,N,r,group", [
+    # one, two and four wavefronts per pair of K blocks: r = 128, one column tile
+    (1, 4096, 300, 128, 128),
+    (1, 2560, 300, 128, 64),
+    (1, 512, 300, 128, 64),
+    # K one pair more than a chunk of four pairs, and an odd number of blocks
+    (1, 640, 9000, 64, 128),
+    (2, 448, 17000, 32, 64),
+    (2, 2048, 9000, 16, 64),
+    # up to eight tokens: fewer rank tiles than wavefronts of a pair, and as many
+    (5, 320, 9000, 16, 64),
+    (7, 1152, 300, 64, 128),
+    # two token blocks, eight wavefronts per pair: a single K block, whole and
+    # broken chunks of two pairs
+    (12, 64, 17000, 64, 64),
+    (16, 1280, 16500, 0, 128),
+    (9, 384, 16500, 128, 64),
+])
+def test_wavefronts_per_pair(oracle_mod, M, K, N, r, group):
+    """Short and long K at each way a pair's tiles are shared out: H bit-exact,
+    the same bits out of the codes and the fp16 activations."""
+    say(f"decode split M={M} K={K} N={N} r={r} group={group}")
+    d = random_codes_layer(M, K, N, r, seed=M + N + r)
+    args = (d["X"], d["W_res"], d["L1"], d["L2"])
+    g, _ = full_parity(oracle_mod, *args, group=group)
+    assert g["kernel"] == "decode"
+    g2 = run_gpu(*args, debug=False, fused_quant=True, group=group)
+    np.testing.assert_array_equal(g["Ybits"], g2["Ybits"])
