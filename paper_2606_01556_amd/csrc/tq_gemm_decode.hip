@@ -38,7 +38,8 @@
 // take block A's codes in k < 64 and rows 8-15 block B's in k >= 64 (zeros
 // elsewhere), so one product yields both blocks' sums (A in lanes 0-31, B in
 // lanes 32-63).  Only the accumulator rows that hold real tokens (MV of the
-// four per lane) are rescaled.  9 to 16 tokens are two token blocks in the grid.
+// four per lane) are rescaled.  9 to 16 tokens are two token blocks of half
+// of them each in the grid.
 //
 // What bounds it.  At these sizes a CU's vector ALU (a 4-bit operand takes 12
 // integer instructions of four cycles to expand, three quarters of a tile's
@@ -220,7 +221,7 @@ __device__ __forceinline__ uint32_t d_load2(__amdgpu_buffer_rsrc_t rsrc, uint32_
 
 template <int MODE, int R, int CT, int S>
 __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
-                                                                   const uint16_t *__restrict__ xh) {
+                                                                   const uint16_t *__restrict__ xh, int mb) {
   using C = DCfg<MODE, R, CT, S>;
   using MD = DMode<MODE>;
   constexpr int MX = MD::MX, MV = MD::MV, XB = MD::XB, PCH = C::PCH, GL = C::GL;
@@ -231,18 +232,21 @@ __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane >> 4, c16 = lane & 15, qh = q & 1, gq = q >> 1;
   const int KG = geo.k / kGroup, NP = (KG + 1) / 2, NCH = (NP + PCH - 1) / PCH;
-  // Column block and token block (8 tokens from m0 on, m of them live).  Two
+  // Column block and token block (mb tokens from m0 on, m of them live).  Two
   // token blocks read the same weights: work-groups are dealt round-robin to
   // the 8 XCDs, so the two of a column block are placed on one, whose L2 then
-  // serves the second.
+  // serves the second -- if the two run in step, so they get half the tokens
+  // each: with 8 + 1 the block with one token to quantize ran ahead and the
+  // weights were fetched twice (8192 -> 28672 r = 0 from fp16, 9 tokens: 38 us;
+  // 5 + 4: 26.5).
   int cblk = blockIdx.x, m0 = 0;
   if (a.m > 8) {
     const int nwg = gridDim.x, per = nwg / 8, rem = nwg % 8, x = blockIdx.x % 8, i = blockIdx.x / 8;
     const int logical = (x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per) + i;
     cblk = logical / 2;
-    m0 = logical % 2 * 8;
+    m0 = logical % 2 * mb;
   }
-  const int m = min(a.m - m0, 8);
+  const int m = min(a.m - m0, mb);
   const int r = geo.r, gk = geo.gk;
   const int ct16 = geo.n_pad / 16;
   const int c0 = cblk * CT;
@@ -800,7 +804,9 @@ hipError_t launch_decode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
   auto kern = dual_gemm_decode_kernel<MODE, R, CT, S>;
   hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), LY.total);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((tiles16 + CT - 1) / CT * ((a.m + 7) / 8)), dim3(64 * DW), LY.total, s, a, xh);
+  const int blocks = (a.m + 7) / 8;
+  hipLaunchKernelGGL(kern, dim3((tiles16 + CT - 1) / CT * blocks), dim3(64 * DW), LY.total, s, a, xh,
+                     blocks == 2 ? (a.m + 1) / 2 : 8);
   return hipGetLastError();
 }
 

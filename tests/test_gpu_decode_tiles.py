@@ -68,3 +68,16 @@ def test_wavefronts_per_pair(oracle_mod, M, K, N, r, group):
     assert g["kernel"] == "decode"
     g2 = run_gpu(*args, debug=False, fused_quant=True, group=group)
     np.testing.assert_array_equal(g["Ybits"], g2["Ybits"])
+
+
+@pytest.mark.parametrize("M,K,N,r", [(9, 192, 100, 64), (11, 320, 8200, 16), (15, 128, 300, 0)])
+def test_odd_token_blocks(oracle_mod, M, K, N, r):
+    """9 to 15 tokens, an odd number: the first token block has one more than the
+    second; H of both blocks bit-exact."""
+    say(f"decode token blocks M={M} K={K} N={N} r={r}")
+    d = random_codes_layer(M, K, N, r, seed=M + N + r)
+    args = (d["X"], d["W_res"], d["L1"], d["L2"])
+    g, _ = full_parity(oracle_mod, *args)
+    assert g["kernel"] == "decode"
+    g2 = run_gpu(*args, debug=False, fused_quant=True)
+    np.testing.assert_array_equal(g["Ybits"], g2["Ybits"])
