@@ -327,6 +327,11 @@ __global__ __launch_bounds__(64 * MW, 2) void dual_gemm_mid_kernel(GemmArgs a, i
         }
 #pragma unroll
         for (int i = 0; i < IP; i++) {
+          // the rest of the last chunk lies past K (the scale operands hold four
+          // groups).  Walked to its end, its zeros cost a K of 128 fourteen
+          // blocks' time and one of 1280 twelve: 1280 -> 4096, r = 128,
+          // M = 128 10.3 us, 9.5 without
+          if (i > 0 && i % 4 == 0 && c * C::CI + ph * IP + i >= KQ) break;
           const int s = u * IP + i;
 #pragma unroll
           for (int t = 0; t < TB; t++) {

@@ -50,3 +50,15 @@ def test_in_place_of_large_blocks(oracle_mod, M, K, N, r, group, kernel):
     d = random_codes_layer(M, K, N, r, seed=M + N + r)
     g, _ = full_parity(oracle_mod, d["X"], d["W_res"], d["L1"], d["L2"], group=group)
     assert g["kernel"] == kernel
+
+
+@pytest.mark.parametrize("M,N,r", [(33, 300, 128), (200, 8000, 64)])
+@pytest.mark.parametrize("K,group", [(128, 64), (256, 64), (320, 64), (768, 64), (1088, 64), (1408, 64),
+                                     (128, 128), (640, 128), (1024, 128), (1152, 128)])
+def test_end_of_k(oracle_mod, M, N, r, K, group):
+    """The last chunk of K ends with the four groups that hold the last block: one
+    block in it, four, five, twelve; 32- and 64-token blocks."""
+    say(f"mid end of K M={M} K={K} N={N} r={r} group={group}")
+    d = random_codes_layer(M, K, N, r, seed=M + K)
+    g, _ = full_parity(oracle_mod, d["X"], d["W_res"], d["L1"], d["L2"], group=group)
+    assert g["kernel"] == "mid"
