@@ -205,7 +205,8 @@ int tq_dual_gemm_kernel(const tq_weight_desc *d, int m);
  *              m > 512, TQ_KERNEL_MID serves any m; TQ_ERR_SHAPE otherwise)
  *   mid_tiles  0: the mid kernel's own choice of token and column tiles per
  *              work-group; 1, 2 or 4 forces 32 tokens and that many 32-column
- *              tiles (TQ_ERR_SHAPE otherwise)
+ *              tiles wherever TQ_KERNEL_MID runs, and has no effect on the
+ *              others (TQ_ERR_SHAPE otherwise)
  *   h, sh, qh  all NULL, or all set (r > 0, else TQ_ERR_RANK) to copy the
  *              low-rank intermediate of every token out of the kernel:
  *                h   [m,r] fp32     H before re-quantization

@@ -87,7 +87,9 @@ hipError_t launch_dual_gemm(const GemmArgs &a, hipStream_t s) {
       // ascending order where they take less time (few blocks, or a last round
       // that is nearly empty): LLaMA3-8B q/o_proj, r = 128 in 128-wide groups,
       // M = 576: 58 -> 43 us
-      if (a.force_kernel < 0 && dual_gemm_mid_ns(a) < block_kernel_ns(a, kernel))
+      // (a forced tile count has a plan of its own, which may sum in parts: it
+      // applies where the mid kernel runs under its own name)
+      if (a.force_kernel < 0 && a.mid_ct == 0 && dual_gemm_mid_ns(a) < block_kernel_ns(a, kernel))
         return launch_dual_gemm_mid(a, true, s);
       return kernel == kKernelLarge ? launch_dual_gemm_large(a, s) : launch_dual_gemm_prefill(a, s);
   }

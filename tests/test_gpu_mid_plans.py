@@ -62,3 +62,21 @@ def test_end_of_k(oracle_mod, M, N, r, K, group):
     d = random_codes_layer(M, K, N, r, seed=M + K)
     g, _ = full_parity(oracle_mod, d["X"], d["W_res"], d["L1"], d["L2"], group=group)
     assert g["kernel"] == "mid"
+
+
+@pytest.mark.parametrize("M,K,N,r,kernel", [(1025, 512, 4100, 16, "large"), (577, 256, 14300, 128, "prefill")])
+def test_forced_tiles_leave_other_kernels(M, K, N, r, kernel):
+    """mid_tiles of the debug entry applies to the mid kernel: where another kernel
+    is named, Y is that kernel's to the bit, not a sum over parts of K."""
+    say(f"forced tiles M={M} K={K} N={N} r={r}")
+    gen = torch.Generator("cuda").manual_seed(M)
+    draw = lambda *s: torch.randn(*s, generator=gen, device="cuda").half()
+    lay = tq.Layer(draw(N, K), draw(K, r), draw(r, N))
+    assert tq.dual_gemm_kernel(lay.desc, M) == kernel
+    xc, xs = tq.empty_act(M, K)
+    tq.quant_act(draw(M, K), xc, xs)
+    y = {}
+    for name, tiles in ((kernel, 0), (None, 1), (None, 2), (None, 4)):
+        y[tiles] = torch.empty((M, N), dtype=torch.half, device="cuda")
+        tq.dual_gemm_debug(lay.desc, lay.packed, xc, xs, M, y[tiles], kernel=name, mid_tiles=tiles)
+        assert torch.equal(y[tiles].view(torch.int16), y[0].view(torch.int16)), tiles
