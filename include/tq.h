@@ -194,6 +194,11 @@ typedef enum {
  * tolerance the fp32 accumulation allows). */
 int tq_dual_gemm_kernel(const tq_weight_desc *d, int m);
 
+/* The block of Y a work-group of that launch owns, (tokens << 16) | columns, or
+ * -1 as above: tells tests and measurements which of a kernel's forms runs.
+ * Host-only; launches nothing. */
+int tq_dual_gemm_block(const tq_weight_desc *d, int m);
+
 /* The same computation as tq_dual_gemm, for tests and measurements:
  *   x          NULL: the activations are x_codes / x_scales as in
  *              tq_dual_gemm; otherwise (x_codes and x_scales NULL) the fp16

@@ -43,7 +43,7 @@ class WeightDesc(ctypes.Structure):
 EXPORTS = ("tq_weight_desc_init", "tq_pack_weights", "tq_quant_act", "tq_dual_gemm",
            "tq_dual_gemm_fused_quant", "tq_dual_gemm_debug", "tq_export_weights",
            "tq_act_codes_bytes", "tq_unfused_scratch_bytes", "tq_dual_gemm_unfused",
-           "tq_dual_gemm_unfused_noalloc", "tq_dual_gemm_kernel", "tq_status_string",
+           "tq_dual_gemm_unfused_noalloc", "tq_dual_gemm_kernel", "tq_dual_gemm_block", "tq_status_string",
            "tq_export_weights_canonical", "tq_act_codes_canonical", "tq_layer",
            "tq_layer_scratch_bytes")
 
@@ -70,6 +70,7 @@ def lib() -> ctypes.CDLL:
         L.tq_act_codes_bytes.restype = ctypes.c_size_t
         L.tq_dual_gemm_kernel.argtypes = [D, I]
         L.tq_dual_gemm_kernel.restype = I
+        L.tq_dual_gemm_block.argtypes = [D, I]
         L.tq_unfused_scratch_bytes.argtypes = [D, I]
         L.tq_unfused_scratch_bytes.restype = ctypes.c_size_t
         L.tq_dual_gemm_unfused.argtypes = [D, P, P, P, I, P, I, P, P]
@@ -360,6 +361,15 @@ def dual_gemm_kernel(desc: WeightDesc, m: int) -> str:
     if k < 0:
         raise ValueError(f"tq_dual_gemm_kernel: invalid descriptor or m = {m}")
     return KERNEL_NAMES[k]
+
+
+def dual_gemm_block(desc: WeightDesc, m: int) -> tuple[int, int]:
+    """(tokens, columns) of Y that a work-group of tq_dual_gemm's launch owns for
+    m tokens (tq_dual_gemm_block); raises ValueError as dual_gemm_kernel."""
+    b = int(lib().tq_dual_gemm_block(ctypes.byref(desc), m))
+    if b < 0:
+        raise ValueError(f"tq_dual_gemm_block: invalid descriptor or m = {m}")
+    return b >> 16, b & 0xffff
 
 
 @functools.lru_cache(maxsize=256)

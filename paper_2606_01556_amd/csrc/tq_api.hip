@@ -222,14 +222,24 @@ static tq_status dual_gemm_impl(const tq_weight_desc *d, const void *packed, con
   return hip_status(tq::launch_dual_gemm(a, s));
 }
 
-int tq_dual_gemm_kernel(const tq_weight_desc *d, int m) {
-  if (d == nullptr || !desc_ok(d) || m < 1 || m > (1 << 24)) return -1;
-  tq::GemmArgs a{};
+// what the kernel choice looks at, for d and m tokens
+static bool choice_args(const tq_weight_desc *d, int m, tq::GemmArgs &a) {
+  if (d == nullptr || !desc_ok(d) || m < 1 || m > (1 << 24)) return false;
   a.geo = geometry(d);
   a.m = m;
   a.ms = (m + 31) / 32 * 32;
   a.force_kernel = -1;
-  return tq::choose_kernel(a);
+  return true;
+}
+
+int tq_dual_gemm_kernel(const tq_weight_desc *d, int m) {
+  tq::GemmArgs a{};
+  return choice_args(d, m, a) ? tq::choose_kernel(a) : -1;
+}
+
+int tq_dual_gemm_block(const tq_weight_desc *d, int m) {
+  tq::GemmArgs a{};
+  return choice_args(d, m, a) ? tq::dual_gemm_block(a) : -1;
 }
 
 size_t tq_act_codes_bytes(int m, int k) {

@@ -60,21 +60,40 @@ int choose_kernel(const GemmArgs &a) {
 }
 
 // Time of a large or prefill launch in ns, to compare with the mid kernel's
-// plans that sum Y in the same ascending order: rounds of blocks x a time per
-// 64-wide K block for the large kernel, one H pass and the run's blocks for
-// the prefill kernel (measured at K = 4096 and 14336, N = 4096 and 14336, M =
-// 576 to 4096, within 10 %).
+// plans that sum Y in the same ascending order, by group width and rank (0, up
+// to 64, 128): rounds of blocks x a part of its own and a time per 64-wide K
+// block for the large kernel; the H pass and the run's blocks for the prefill
+// kernel.  Fitted to 2600 calls with K 512 to 16384, N 256 to 16384 and M 513 to
+// 4096, 95 % of them within 12 %.
 int64_t block_kernel_ns(const GemmArgs &a, int kernel) {
-  const int m_tiles = (a.m + 127) / 128, n_tiles = (a.geo.n_pad + 255) / 256;
+  const int64_t m_tiles = (a.m + 127) / 128, n_tiles = (a.geo.n_pad + 255) / 256;
   const int rt = a.geo.r_pad32 / 32, c = rt == 0 ? 0 : (rt <= 2 ? 1 : 2), g2 = a.geo.gk == 2;
   const int64_t kg = a.geo.k / 64;
   if (kernel == kKernelLarge) {
-    constexpr int kBlock[2][3] = {{680, 800, 970}, {460, 740, 760}};
-    return ((int64_t)m_tiles * n_tiles + 255) / 256 * (10000 + kg * kBlock[g2][c]);
+    constexpr int kRound[2][3] = {{5300, 7600, 10400}, {5000, 7300, 9900}};
+    constexpr int kBlock[2][3] = {{600, 700, 885}, {466, 790, 756}};
+    return 900 + (m_tiles * n_tiles + 255) / 256 * (kRound[g2][c] + kg * kBlock[g2][c]);
   }
-  constexpr int kPass[3] = {0, 250, 420};
-  const int runs = m_tiles >= 256 ? 1 : 256 / m_tiles, cpw = (n_tiles + runs - 1) / runs;
-  return 6000 + kg * (kPass[c] + (g2 ? 620 : 700) * (int64_t)cpw) * ((m_tiles + 255) / 256);
+  // launch, column block, H pass and column block per K block
+  constexpr int kNs[2][3][4] = {{{3400, 3900, -100, 565}, {8100, 5300, 150, 570}, {12700, 5400, 310, 563}},
+                                {{3000, 4000, -80, 468}, {8100, 5300, 140, 448}, {12600, 5000, 255, 465}}};
+  const int *t = kNs[g2][c];
+  const int64_t runs = m_tiles >= 256 ? 1 : 256 / m_tiles, cpw = (n_tiles + runs - 1) / runs;
+  return (t[0] + t[1] * cpw + kg * (t[2] + t[3] * cpw)) * ((m_tiles + 255) / 256);
+}
+
+// Whether the mid kernel's blocks take the place of `kernel`'s (same sums).  They
+// have to be 2 % cheaper: of 1380 such calls timed, 45 % are then replaced, at
+// 0.87 of the time on average; 10 of them are slower, by 2 to 9 %.
+bool mid_in_place(const GemmArgs &a, int kernel) {
+  return a.force_kernel < 0 && a.mid_ct == 0 && 50 * dual_gemm_mid_ns(a) < 49 * block_kernel_ns(a, kernel);
+}
+
+int dual_gemm_block(const GemmArgs &a) {
+  const int kernel = choose_kernel(a);
+  if (kernel == kKernelDecode) return dual_gemm_decode_block(a);
+  const bool exact = kernel != kKernelMid;
+  return !exact || mid_in_place(a, kernel) ? dual_gemm_mid_block(a, exact) : 128 << 16 | 256;
 }
 
 hipError_t launch_dual_gemm(const GemmArgs &a, hipStream_t s) {
@@ -86,11 +105,9 @@ hipError_t launch_dual_gemm(const GemmArgs &a, hipStream_t s) {
       // 128 x 256 blocks, or the mid kernel's smaller ones with Y in the same
       // ascending order where they take less time (few blocks, or a last round
       // that is nearly empty): LLaMA3-8B q/o_proj, r = 128 in 128-wide groups,
-      // M = 576: 58 -> 43 us
-      // (a forced tile count has a plan of its own, which may sum in parts: it
-      // applies where the mid kernel runs under its own name)
-      if (a.force_kernel < 0 && a.mid_ct == 0 && dual_gemm_mid_ns(a) < block_kernel_ns(a, kernel))
-        return launch_dual_gemm_mid(a, true, s);
+      // M = 576: 58 -> 43 us.  A forced tile count has a plan of its own, which
+      // may sum in parts: it applies where the mid kernel runs under its own name.
+      if (mid_in_place(a, kernel)) return launch_dual_gemm_mid(a, true, s);
       return kernel == kKernelLarge ? launch_dual_gemm_large(a, s) : launch_dual_gemm_prefill(a, s);
   }
 }

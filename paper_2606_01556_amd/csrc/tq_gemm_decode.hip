@@ -795,6 +795,9 @@ __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
   }
 }
 
+// tokens of a token block
+int decode_block_tokens(int m) { return m <= 8 ? 8 : (m + 1) / 2; }
+
 template <int MODE, int R, int CT, int S>
 hipError_t launch_decode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
   using C = DCfg<MODE, R, CT, S>;
@@ -804,9 +807,8 @@ hipError_t launch_decode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
   auto kern = dual_gemm_decode_kernel<MODE, R, CT, S>;
   hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), LY.total);
   if (e != hipSuccess) return e;
-  const int blocks = (a.m + 7) / 8;
-  hipLaunchKernelGGL(kern, dim3((tiles16 + CT - 1) / CT * blocks), dim3(64 * DW), LY.total, s, a, xh,
-                     blocks == 2 ? (a.m + 1) / 2 : 8);
+  hipLaunchKernelGGL(kern, dim3((tiles16 + CT - 1) / CT * ((a.m + 7) / 8)), dim3(64 * DW), LY.total, s, a, xh,
+                     decode_block_tokens(a.m));
   return hipGetLastError();
 }
 
@@ -856,12 +858,16 @@ hipError_t launch_decode_r(int ct, const GemmArgs &a, const uint16_t *xh, hipStr
   }
 }
 
+// the fewest 16-column tiles per work-group that keep the grid within one
+// work-group per CU
+int decode_tiles(const GemmArgs &a) {
+  const int tiles16 = a.geo.n_pad / 16 * ((a.m + 7) / 8);
+  return tiles16 <= 256 ? 1 : (tiles16 <= 512 ? 2 : (tiles16 <= 1024 ? 4 : (tiles16 <= 2048 ? 8 : 16)));
+}
+
 template <int MODE>
 hipError_t launch_decode_mode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
-  // the fewest 16-column tiles per work-group that keep the grid within one
-  // work-group per CU
-  const int tiles16 = a.geo.n_pad / 16 * ((a.m + 7) / 8);
-  const int ct = tiles16 <= 256 ? 1 : (tiles16 <= 512 ? 2 : (tiles16 <= 1024 ? 4 : (tiles16 <= 2048 ? 8 : 16)));
+  const int ct = decode_tiles(a);
   switch (rank_tiles(a.geo.r)) {
     case 0: return launch_decode_r<MODE, 0>(ct, a, xh, s);
     case 1: return launch_decode_r<MODE, 1>(ct, a, xh, s);
@@ -883,6 +889,8 @@ bool decode_fits(int m, int k) {
   const int64_t kgp = (int64_t)(k / kGroup + 1) / 2 * 2;
   return kgp * bytes <= kDecodeXBytes;
 }
+
+int dual_gemm_decode_block(const GemmArgs &a) { return decode_block_tokens(a.m) << 16 | 16 * decode_tiles(a); }
 
 // xh: fp16 activations to quantize in the kernel, or NULL: codes from a.xc / a.xs
 hipError_t launch_dual_gemm_decode(const GemmArgs &a, const uint16_t *xh, hipStream_t s) {

@@ -569,18 +569,37 @@ hipError_t launch_mid_rt(int tb, int ct, const GemmArgs &a, hipStream_t s) {
 // 320 at every rank (four tile-groups per SIMD).  128-wide groups take 0.85
 // of that (one rescale per two blocks).
 struct MidPlan {
-  int tb, ct, ns;   // token tiles, column tiles (TB = 2: all columns that hold no H), time
+  int tb, ct;   // token tiles, column tiles (TB = 2: all columns that hold no H)
+  int64_t ns;   // time
 };
+
+int64_t mid_rounds(const GemmArgs &a, int tb, int ct) {
+  const int64_t n_wg = (int64_t)((a.ms / 32 + tb - 1) / tb) * ((a.geo.n_pad / 32 + ct - 1) / ct);
+  return (n_wg + 255) / 256;
+}
 
 MidPlan mid_cost(const GemmArgs &a, int tb, int ct) {
   const int rt = a.geo.r_pad32 / 32, c = rt == 0 ? 0 : (rt <= 2 ? 1 : 2);
-  const int n_wg = (a.ms / 32 + tb - 1) / tb * ((a.geo.n_pad / 32 + ct - 1) / ct);
   constexpr int kBlock[3][3] = {{70, 112, 130}, {107, 156, 190}, {320, 320, 310}};
   int block = kBlock[tb == 2 ? 2 : (ct == 4 ? 1 : 0)][c];
   if (a.geo.gk == 2) block = block * 85 / 100;
   const int64_t round = (tb == 2 ? 6000 : 3500) + (int64_t)block * (a.geo.k / 64);
-  const int64_t ns = 3000 + (n_wg + 255) / 256 * round;
-  return MidPlan{tb, ct, ns < (1 << 30) ? (int)ns : 1 << 30};
+  return MidPlan{tb, ct, 3000 + mid_rounds(a, tb, ct) * round};
+}
+
+// The same for the plans whose wavefronts own their column tiles alone, fitted
+// past 512 tokens (fp8 codes) to 2600 calls with K 512 to 16384, N 256 to 16384
+// and M 513 to 4096, 95 % of them within 10 %: a launch, a round, a 64-wide
+// block of K by group width, token tiles and rank (0, up to 64, 128).
+MidPlan mid_exact_cost(const GemmArgs &a, int tb, int ct) {
+  const int rt = a.geo.r_pad32 / 32, c = rt == 0 ? 0 : (rt <= 2 ? 1 : 2);
+  constexpr int kNs[2][2][3][3] = {
+      {{{2260, 2370, 105}, {2200, 4280, 162}, {1900, 5620, 188}},
+       {{1840, 4010, 305}, {1520, 6320, 293}, {2380, 7360, 292}}},
+      {{{2250, 2840, 92}, {2120, 4490, 132}, {1840, 5450, 149}},
+       {{1510, 4460, 260}, {1820, 6410, 250}, {2320, 7060, 251}}}};
+  const int *t = kNs[a.geo.gk - 1][tb - 1][c];
+  return MidPlan{tb, ct, t[0] + mid_rounds(a, tb, ct) * (t[1] + (int64_t)t[2] * (a.geo.k / 64))};
 }
 
 // the plan of least time; exact: only those whose wavefronts own their column
@@ -588,9 +607,14 @@ MidPlan mid_cost(const GemmArgs &a, int tb, int ct) {
 MidPlan mid_plan(const GemmArgs &a, bool exact) {
   const int rt = a.geo.r_pad32 / 32;
   if (a.mid_ct > 0) return MidPlan{1, a.mid_ct, 0};   // forced by the test entry (1, 2 or 4, validated there)
+  if (exact) {
+    const MidPlan wide = mid_exact_cost(a, 2, MW - rt);
+    if (rt == 0) return wide;   // (32 tokens x four column tiles share K there)
+    const MidPlan p = mid_exact_cost(a, 1, 4);
+    return p.ns < wide.ns ? p : wide;
+  }
   MidPlan best = mid_cost(a, 2, MW - rt);
   for (int ct : {1, 2, 4}) {
-    if (exact && (ct != 4 || rt == 0)) continue;
     const MidPlan p = mid_cost(a, 1, ct);
     if (p.ns < best.ns) best = p;
   }
@@ -599,7 +623,12 @@ MidPlan mid_plan(const GemmArgs &a, bool exact) {
 
 }  // namespace
 
-int dual_gemm_mid_ns(const GemmArgs &a) { return mid_plan(a, true).ns; }
+int64_t dual_gemm_mid_ns(const GemmArgs &a) { return mid_plan(a, true).ns; }
+
+int dual_gemm_mid_block(const GemmArgs &a, bool exact) {
+  const MidPlan p = mid_plan(a, exact);
+  return 32 * p.tb << 16 | 32 * p.ct;
+}
 
 hipError_t launch_dual_gemm_mid(const GemmArgs &a, bool exact, hipStream_t s) {
   const MidPlan p = mid_plan(a, exact);

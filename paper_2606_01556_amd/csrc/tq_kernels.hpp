@@ -81,10 +81,14 @@ bool decode_fits(int m, int k);
 // the kernel launch_dual_gemm runs (values of tq_kernel in the C header)
 constexpr int kKernelDecode = 0, kKernelMid = 1, kKernelLarge = 2, kKernelPrefill = 3;
 int choose_kernel(const GemmArgs &a);
+// tokens << 16 | columns of the work-groups that kernel is launched with
+int dual_gemm_block(const GemmArgs &a);
+int dual_gemm_decode_block(const GemmArgs &a);
+int dual_gemm_mid_block(const GemmArgs &a, bool exact);
 // mid sizes; exact: Y summed in ascending group order
 hipError_t launch_dual_gemm_mid(const GemmArgs &a, bool exact, hipStream_t s);
 // estimated time in ns of the mid kernel's best plan with that order
-int dual_gemm_mid_ns(const GemmArgs &a);
+int64_t dual_gemm_mid_ns(const GemmArgs &a);
 hipError_t launch_dual_gemm_prefill(const GemmArgs &a, hipStream_t s);  // prefill sizes
 hipError_t launch_dual_gemm_large(const GemmArgs &a, hipStream_t s);    // large token counts
 // the layer without fusion (comparison baseline): residual GEMM, stage 1 to

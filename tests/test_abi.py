@@ -319,3 +319,25 @@ def test_kernel_choice(L):
     assert L.tq_dual_gemm_kernel(None, 100) == -1
     with pytest.raises(ValueError):
         tq.dual_gemm_kernel(d, 0)
+
+
+def test_block_choice(L):
+    """tq_dual_gemm_block: the decode kernel's fewest column tiles that fit one
+    round over the 256 CUs; the mid kernel's plans; 128 x 256 blocks, or the mid
+    kernel's where those take less time by the model -- which is not cut off:
+    a call of more than a second by it keeps its large blocks."""
+    block = lambda n, k, r, m, group=64: tq.dual_gemm_block(tq.weight_desc_init(n, k, r, group), m)
+    assert [block(n, 4096, 64, 1) for n in (4096, 4097, 8192, 16384, 16416, 32800)] == \
+        [(8, 16), (8, 32), (8, 32), (8, 64), (8, 128), (8, 256)]
+    assert block(4096, 4096, 64, 9) == (5, 32) and block(4096, 4096, 64, 16) == (8, 32)
+    assert block(4096, 4096, 64, 17)[0] == 32 and block(12288, 4096, 64, 256) == (64, 192)
+    assert block(5001, 2880, 16, 777) == (64, 224)
+    assert block(4096, 4096, 64, 2048) == (128, 256) and block(28672, 8192, 128, 8192) == (128, 256)
+    # 32-bit nanoseconds hold 2.1 s, 2^30 of them 1.07 s
+    for n, k, m in ((32768, 32768, 1 << 20), (65536, 65536, 1 << 20), (16384, 16384, 1 << 24)):
+        for r in (64, 128):
+            assert block(n, k, r, m) == (128, 256), (n, k, m, r)
+    bad = tq.WeightDesc()
+    assert L.tq_dual_gemm_block(ctypes.byref(bad), 16) == -1 and L.tq_dual_gemm_block(None, 16) == -1
+    with pytest.raises(ValueError):
+        block(4096, 4096, 64, 0)
