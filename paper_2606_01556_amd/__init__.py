@@ -422,16 +422,22 @@ class Layer:
         """Y = layer(x) for fp16 x [m, k] (tq_layer: the activation quantizer and
         the fused layer)."""
         import torch
+        desc, packed = self.desc, self.packed
         _tensor(x, "x", torch.float16)
         if x.dim() != 2 or x.shape[1] != self.k:
             raise ValueError(f"x: expected [m, {self.k}], got shape {tuple(x.shape)}")
+        # the attributes are the program's to change: packed may have been moved
+        # to the host, desc may be another layer's
+        _tensor(packed, "packed", min_bytes=int(desc.packed_bytes))
+        if desc.k != self.k or desc.n != self.n:
+            raise ValueError(f"desc: {desc.n} x {desc.k}, the layer is {self.n} x {self.k}")
         m = x.shape[0]
         y = x.new_empty((m, self.n), dtype=torch.bfloat16 if bf16 else None)
         scratch = None
         if m > self._one_launch:
-            scratch = x.new_empty((layer_scratch_bytes(m, self.k, self.desc.group) // 2,))
+            scratch = x.new_empty((layer_scratch_bytes(m, self.k, desc.group) // 2,))
         st = _stream(stream)
-        _check(lib().tq_layer(self.desc, self.packed.data_ptr(), x.data_ptr(), m, y.data_ptr(),
+        _check(lib().tq_layer(desc, _ptr(packed), x.data_ptr(), m, y.data_ptr(),
                               TQ_BF16 if bf16 else TQ_F16, None if scratch is None else scratch.data_ptr(), st),
                "tq_layer")
         if stream is not None and scratch is not None and st != _current_stream():

@@ -2,7 +2,6 @@
 scratch sizes on the CPU, the same bits as the quantizer and the fused layer
 called one after the other on the GPU."""
 import copy
-import ctypes
 
 import numpy as np
 import pytest
@@ -39,7 +38,66 @@ def test_validation():
     assert call(t=5) == 5 and call(t=5, m=1) == 5
     assert call(x=FAKE + 8) == 6 and call(s=FAKE + 8) == 6 and call(y=FAKE + 2, m=1) == 6
     assert call(m=0) == 0
-    assert ctypes.sizeof(tq.WeightDesc) > 0
+
+
+class FakeGpuTensor(torch.Tensor):
+    """A host tensor that passes for a GPU one; the stand-in library below takes
+    its address and follows none."""
+    is_cuda = property(lambda self: True)
+
+
+class FakeLib:
+    """Records the pointers of tq_layer; the rest is the library's own."""
+
+    def __init__(self):
+        self.calls, self.real = [], tq.lib()
+
+    def tq_layer(self, *args):
+        self.calls.append(args)
+        return 0
+
+    def __getattr__(self, name):
+        return getattr(self.real, name)
+
+
+@pytest.fixture
+def fake(monkeypatch):
+    """(library, layer, x) for Layer.__call__ without a GPU."""
+    fake = FakeLib()
+    monkeypatch.setattr(tq, "lib", lambda: fake)
+    monkeypatch.setattr(tq, "_current_stream", lambda: 0)
+    gpu = lambda *s, dtype=torch.float16: torch.empty(s, dtype=dtype).as_subclass(FakeGpuTensor)
+    lay = tq.Layer.__new__(tq.Layer)
+    lay.desc = tq.weight_desc_init(96, 512, 16)
+    lay.packed = gpu(lay.desc.packed_bytes, dtype=torch.uint8)
+    lay.n, lay.k, lay.rank = 96, 512, 16
+    lay._one_launch = 16
+    return fake, lay, gpu(3, 512)
+
+
+def test_packed_and_desc_are_checked(fake):
+    """What the library would read out of bounds is refused before the call: packed
+    weights on the host, too short or strided, and a descriptor of other sizes; a
+    raw device address is taken as it is."""
+    L, lay, x = fake
+    packed, desc = lay.packed, lay.desc
+    lay(x)
+    assert len(L.calls) == 1 and L.calls[0][1] == packed.data_ptr()
+    for bad in (torch.empty(packed.numel(), dtype=torch.uint8), packed[:-1],
+                torch.empty(2 * packed.numel(), dtype=torch.uint8).as_subclass(FakeGpuTensor)[::2], None):
+        lay.packed = bad
+        with pytest.raises(ValueError):
+            lay(x)
+    lay.packed = packed
+    for n, k in ((128, 512), (96, 576)):
+        lay.desc = tq.weight_desc_init(n, k, 0)
+        with pytest.raises(ValueError):
+            lay(x)
+    lay.desc = desc
+    assert len(L.calls) == 1
+    lay.packed = FAKE
+    lay(x)
+    assert L.calls[1][1] == FAKE
 
 
 @pytest.mark.gpu
