@@ -385,6 +385,12 @@ def layer_scratch_bytes(m: int, k: int, group: int = GROUP) -> int:
     return (act_codes_bytes(m, k) + 255) // 256 * 256 + padded_tokens(m) * (k // group) * 2
 
 
+@functools.lru_cache(maxsize=256)
+def _layer_scratch(m: int, k: int, group: int) -> int:
+    """tq_layer_scratch_bytes, which depends on no other size of the layer."""
+    return int(lib().tq_layer_scratch_bytes(weight_desc_init(32, k, 0, group), m))
+
+
 def empty_act(m: int, k: int, device="cuda", group: int = GROUP):
     """(x_codes, x_scales) buffers for tq_quant_act / tq_dual_gemm:
     x_codes [m32/32, k/64, W] int32, one tile-major block per 32 tokens and
@@ -413,10 +419,6 @@ class Layer:
         pack_weights(self.desc, w_res.contiguous(), None if l1 is None else l1.contiguous(),
                      None if l2 is None else l2.contiguous(), self.packed, stream)
         self.n, self.k, self.rank = n, k, r
-        # up to this many tokens the layer is one launch and needs no scratch
-        self._one_launch = 0
-        while self._one_launch < 16 and not lib().tq_layer_scratch_bytes(self.desc, self._one_launch + 1):
-            self._one_launch += 1
 
     def __call__(self, x, bf16: bool = False, stream=None):
         """Y = layer(x) for fp16 x [m, k] (tq_layer: the activation quantizer and
@@ -433,9 +435,8 @@ class Layer:
             raise ValueError(f"desc: {desc.n} x {desc.k}, the layer is {self.n} x {self.k}")
         m = x.shape[0]
         y = x.new_empty((m, self.n), dtype=torch.bfloat16 if bf16 else None)
-        scratch = None
-        if m > self._one_launch:
-            scratch = x.new_empty((layer_scratch_bytes(m, self.k, desc.group) // 2,))
+        nscratch = _layer_scratch(m, desc.k, desc.group)
+        scratch = x.new_empty((nscratch // 2,)) if nscratch else None
         st = _stream(stream)
         _check(lib().tq_layer(desc, _ptr(packed), x.data_ptr(), m, y.data_ptr(),
                               TQ_BF16 if bf16 else TQ_F16, None if scratch is None else scratch.data_ptr(), st),

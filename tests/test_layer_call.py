@@ -71,7 +71,6 @@ def fake(monkeypatch):
     lay.desc = tq.weight_desc_init(96, 512, 16)
     lay.packed = gpu(lay.desc.packed_bytes, dtype=torch.uint8)
     lay.n, lay.k, lay.rank = 96, 512, 16
-    lay._one_launch = 16
     return fake, lay, gpu(3, 512)
 
 
@@ -98,6 +97,16 @@ def test_packed_and_desc_are_checked(fake):
     lay.packed = FAKE
     lay(x)
     assert L.calls[1][1] == FAKE
+
+
+def test_only_the_saved_attributes(fake):
+    """A layer needs no more than desc, packed, n, k and rank, which a program may
+    have saved or set by itself; scratch where the size asks for it."""
+    L, lay, x = fake
+    lay(x)
+    assert L.calls[-1][6] is None
+    lay(torch.empty((17, 512), dtype=torch.float16).as_subclass(FakeGpuTensor))
+    assert L.calls[-1][6] is not None
 
 
 @pytest.mark.gpu
