@@ -372,13 +372,13 @@ def dual_gemm_block(desc: WeightDesc, m: int) -> tuple[int, int]:
     return b >> 16, b & 0xffff
 
 
-@functools.lru_cache(maxsize=256)
+@functools.lru_cache(maxsize=256, typed=True)   # (32.0 is refused, also after 32)
 def act_codes_bytes(m: int, k: int) -> int:
     """Bytes of the x_codes buffer of m tokens (tq_act_codes_bytes)."""
     return int(lib().tq_act_codes_bytes(m, k))
 
 
-@functools.lru_cache(maxsize=256)
+@functools.lru_cache(maxsize=256, typed=True)
 def layer_scratch_bytes(m: int, k: int, group: int = GROUP) -> int:
     """Bytes of tq_layer's scratch where it takes two launches: the codes (rounded
     up to 256 bytes) and the scales of m tokens."""

@@ -262,6 +262,16 @@ def test_act_codes_bytes(L):
     assert L.tq_act_codes_bytes(16, 100) == 0 and L.tq_act_codes_bytes(-1, 64) == 0
 
 
+def test_sizes_are_integers():
+    """The sizes kept by argument refuse what the C function refuses, also where
+    an equal integer was asked for before."""
+    for f, args in ((tq.act_codes_bytes, (32, 4096)), (tq.layer_scratch_bytes, (32, 4096))):
+        assert f(*args) > 0
+        for bad in ((32.0, 4096), (32, 4096.0), (np.float64(32), 4096)):
+            with pytest.raises((ctypes.ArgumentError, TypeError)):
+                f(*bad)
+
+
 def test_unfused_sizes_and_validation(L):
     """Scratch of the unfused layer: H fp32 [m32][r_pad32], Q_H [m32][r_pad64],
     s_H [r/group_r][m32], each at a 256-byte-aligned offset; 0 for a bad
