@@ -127,6 +127,18 @@ def _stream(stream):
     return stream.cuda_stream
 
 
+def _other_stream(stream, handle, device):
+    """`stream` (a torch stream or a hipStream_t, `handle` its hipStream_t) as a
+    torch stream of `device`, or None where it is the current one there."""
+    import torch
+    if handle == torch.cuda.current_stream(device).cuda_stream:
+        return None
+    if isinstance(stream, torch.cuda.Stream):
+        return stream
+    # (ExternalStream takes 0 for "none given" and returns a stream of its own)
+    return torch.cuda.ExternalStream(handle, device=device) if handle else torch.cuda.default_stream(device)
+
+
 # ------------------------------------------------------------------ argument checks
 # Every wrapper below checks its tensors before the C call: the library sees
 # only raw pointers and would read or write out of bounds on a wrong shape.
@@ -422,28 +434,44 @@ class Layer:
 
     def __call__(self, x, bf16: bool = False, stream=None):
         """Y = layer(x) for fp16 x [m, k] (tq_layer: the activation quantizer and
-        the fused layer)."""
+        the fused layer), on `stream` (default: the current one).  x has to be
+        ready there; Y is ready when that stream is, and may then be used, and
+        dropped, on the stream that was current in the call."""
         import torch
-        desc, packed = self.desc, self.packed
-        _tensor(x, "x", torch.float16)
-        if x.dim() != 2 or x.shape[1] != self.k:
-            raise ValueError(f"x: expected [m, {self.k}], got shape {tuple(x.shape)}")
+        desc, packed, n, k = self.desc, self.packed, self.n, self.k
+        # (the usual tensors are checked in place: a call through _tensor costs
+        # as much as the rest of these lines)
+        if not (type(x) is torch.Tensor and x.is_cuda and x.dtype is torch.float16 and x.is_contiguous()):
+            _tensor(x, "x", torch.float16)
+        shape = x.shape
+        if len(shape) != 2 or shape[1] != k:
+            raise ValueError(f"x: expected [m, {k}], got shape {tuple(shape)}")
+        m = shape[0]
         # the attributes are the program's to change: packed may have been moved
         # to the host, desc may be another layer's
-        _tensor(packed, "packed", min_bytes=int(desc.packed_bytes))
-        if desc.k != self.k or desc.n != self.n:
-            raise ValueError(f"desc: {desc.n} x {desc.k}, the layer is {self.n} x {self.k}")
-        m = x.shape[0]
-        y = x.new_empty((m, self.n), dtype=torch.bfloat16 if bf16 else None)
-        nscratch = _layer_scratch(m, desc.k, desc.group)
-        scratch = x.new_empty((nscratch // 2,)) if nscratch else None
+        if not (type(packed) is torch.Tensor and packed.is_cuda and packed.is_contiguous()
+                and packed.nbytes >= desc.packed_bytes):
+            _tensor(packed, "packed", min_bytes=int(desc.packed_bytes))
+        if desc.k != k or desc.n != n:
+            raise ValueError(f"desc: {desc.n} x {desc.k}, the layer is {n} x {k}")
         st = _stream(stream)
+        nscratch = _layer_scratch(m, k, desc.group)
+        dtype = torch.bfloat16 if bf16 else None
+        other = None if stream is None else _other_stream(stream, st, x.device)
+        if other is None:
+            y = x.new_empty((m, n), dtype=dtype)
+            scratch = x.new_empty((nscratch // 2,)) if nscratch else None
+        else:
+            # from that stream's memory: a block of the current stream's may still
+            # be in use by the work it was freed behind, which that stream does
+            # not wait for
+            with torch.cuda.stream(other):
+                y = x.new_empty((m, n), dtype=dtype)
+                scratch = x.new_empty((nscratch // 2,)) if nscratch else None
+            y.record_stream(torch.cuda.current_stream(x.device))
         _check(lib().tq_layer(desc, _ptr(packed), x.data_ptr(), m, y.data_ptr(),
                               TQ_BF16 if bf16 else TQ_F16, None if scratch is None else scratch.data_ptr(), st),
                "tq_layer")
-        if stream is not None and scratch is not None and st != _current_stream():
-            # freed here, in use there: its memory waits for that stream
-            scratch.record_stream(torch.cuda.ExternalStream(st, device=x.device))
         return y
 
 

@@ -135,3 +135,47 @@ def test_layer_call(m, k, n, r, group, bf16):
         y = layer(x, bf16, stream=stream)
         torch.cuda.synchronize()
         assert y.dtype == ref.dtype and torch.equal(y.view(torch.int16), ref.view(torch.int16))
+
+
+def stream_of(t):
+    """The hipStream_t whose memory the allocator took t's storage from."""
+    for seg in torch.cuda.memory_snapshot():
+        if seg["address"] <= t.data_ptr() < seg["address"] + seg["total_size"]:
+            return seg["stream"]
+
+
+@pytest.mark.gpu
+def test_other_stream():
+    """A call on another stream than the current one works in that stream's memory
+    -- given as a torch stream, its handle, the default stream and 0 -- so
+    nothing pending on the current stream, where a block of the same size was
+    just freed, can touch its codes or its result."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    gen = torch.Generator("cuda").manual_seed(3)
+    draw = lambda *s: torch.randn(*s, generator=gen, device="cuda").half()
+    m, k, n = 600, 1024, 1000
+    lay = tq.Layer(draw(n, k), draw(k, 32), draw(32, n))
+    x = draw(m, k)
+    want = lay(x)
+    torch.cuda.synchronize()
+    side, here = torch.cuda.Stream(), torch.cuda.Stream()
+    default = torch.cuda.default_stream()
+    busy = torch.randn(2048, 2048, device="cuda")
+    for current, given in ((default, side), (default, side.cuda_stream), (here, side), (here, default), (here, 0)):
+        print("[case] current", current, "given", given, flush=True)
+        with torch.cuda.stream(current):
+            handle = given if isinstance(given, int) else given.cuda_stream
+            old = [torch.empty(b, dtype=torch.uint8, device="cuda")
+                   for b in (tq.layer_scratch_bytes(m, k), m * n * 2)]
+            for _ in range(20):
+                busy = busy @ busy * 1e-3
+            for t in old:
+                t.fill_(0x77)          # behind the products: pending when freed
+            del old, t
+            y = lay(x, stream=given)
+            assert stream_of(y) == handle
+            torch.cuda.ExternalStream(handle).synchronize() if handle else default.synchronize()
+            assert torch.equal(y.view(torch.int16), want.view(torch.int16))
+        torch.cuda.synchronize()
+    assert stream_of(lay(x, stream=default)) == default.cuda_stream      # the current one, by its name
