@@ -457,17 +457,18 @@ class Layer:
         st = _stream(stream)
         nscratch = _layer_scratch(m, k, desc.group)
         dtype = torch.bfloat16 if bf16 else None
+        new = (x if type(x) is torch.Tensor else x.as_subclass(torch.Tensor)).new_empty   # Y is a plain tensor
         other = None if stream is None else _other_stream(stream, st, x.device)
         if other is None:
-            y = x.new_empty((m, n), dtype=dtype)
-            scratch = x.new_empty((nscratch // 2,)) if nscratch else None
+            y = new((m, n), dtype=dtype)
+            scratch = new((nscratch // 2,)) if nscratch else None
         else:
             # from that stream's memory: a block of the current stream's may still
             # be in use by the work it was freed behind, which that stream does
             # not wait for
             with torch.cuda.stream(other):
-                y = x.new_empty((m, n), dtype=dtype)
-                scratch = x.new_empty((nscratch // 2,)) if nscratch else None
+                y = new((m, n), dtype=dtype)
+                scratch = new((nscratch // 2,)) if nscratch else None
             y.record_stream(torch.cuda.current_stream(x.device))
         _check(lib().tq_layer(desc, _ptr(packed), x.data_ptr(), m, y.data_ptr(),
                               TQ_BF16 if bf16 else TQ_F16, None if scratch is None else scratch.data_ptr(), st),

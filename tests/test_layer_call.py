@@ -99,6 +99,14 @@ def test_packed_and_desc_are_checked(fake):
     assert L.calls[1][1] == FAKE
 
 
+def test_result_is_a_plain_tensor(fake):
+    """Also for activations of a tensor subclass."""
+    L, lay, x = fake
+    assert type(x) is FakeGpuTensor and type(lay(x)) is torch.Tensor
+    y = lay(x, bf16=True)
+    assert type(y) is torch.Tensor and y.dtype == torch.bfloat16 and y.shape == (3, 96)
+
+
 def test_only_the_saved_attributes(fake):
     """A layer needs no more than desc, packed, n, k and rank, which a program may
     have saved or set by itself; scratch where the size asks for it."""
