@@ -166,7 +166,8 @@ tq_status tq_dual_gemm_fused_quant(const tq_weight_desc *d, const void *packed, 
  * codes and scales in `scratch`.  The results are the same bits either way.
  *   scratch  device buffer of tq_layer_scratch_bytes(d, m) bytes, 16-byte
  *            aligned, owned by the caller and free again when the stream has
- *            run the call; may be NULL where that size is 0
+ *            run the call; may be NULL where that size is 0, and for m = 1 with
+ *            k <= 114688 (one launch then, slower than two past k = 32768)
  * m == 0 is a no-op.  Errors as tq_quant_act and tq_dual_gemm (TQ_ERR_NULL for a
  * NULL scratch that is needed). */
 size_t tq_layer_scratch_bytes(const tq_weight_desc *d, int m);

@@ -279,13 +279,15 @@ tq_status tq_dual_gemm_debug(const tq_weight_desc *d, const void *packed, const 
 }
 
 // Whole-layer calls up to 16 tokens quantize inside the layer's launch where
-// that costs less than a launch of its own: every work-group then quantizes its
-// block of up to 8 tokens itself, 0.11 us per 1000 values, against 3 to 4 us for
-// the quantizer's launch and the gap behind it (K = 14336: 8 tokens 35 us in
-// one launch, 27 in two; K = 4096: 11.6 and 13).
+// that costs no more than a launch of its own: every work-group then quantizes
+// its block of up to 8 tokens itself, 0.07 to 0.1 us per 1000 values, against 2
+// to 3 us for the quantizer's launch and the gap behind it (us, one launch less
+// two, mean over N 1024 to 16384 and r 0 to 128: one token K = 8192 -1.9, 28672
+// -0.4, 49152 +1.0, 114688 +6.0; 8 tokens K = 4096 +0.9, 8192 +4.5).  At the
+// line a second launch costs the host more than the difference.
 static bool layer_one_launch(int m, int k) {
   return m >= 1 && m <= tq::kDecodeMaxTokens && tq::decode_fits(m, k) &&
-         (m == 1 || (int64_t)(m < 8 ? m : 8) * k <= 32768);
+         (int64_t)(m < 8 ? m : 8) * k <= 32768;
 }
 
 size_t tq_layer_scratch_bytes(const tq_weight_desc *d, int m) {
@@ -299,7 +301,9 @@ tq_status tq_layer(const tq_weight_desc *d, const void *packed, const void *x, i
   if (d == nullptr || packed == nullptr || x == nullptr || y == nullptr) return TQ_ERR_NULL;
   if (!desc_ok(d)) return TQ_ERR_BUFFER;
   if (m < 0 || m > 65535 * 32) return TQ_ERR_SHAPE;
-  if (layer_one_launch(m, d->k)) return tq_dual_gemm_fused_quant(d, packed, x, m, y, y_dtype, stream);
+  // (one token needs no scratch at any K that fits: without it, one launch)
+  if (layer_one_launch(m, d->k) || (scratch == nullptr && m == 1 && tq::decode_fits(m, d->k)))
+    return tq_dual_gemm_fused_quant(d, packed, x, m, y, y_dtype, stream);
   if (y_dtype != TQ_F16 && y_dtype != TQ_BF16) return TQ_ERR_DTYPE;
   if (!aligned16(packed) || !aligned16(x) || !aligned16(y) || !aligned16(scratch)) return TQ_ERR_ALIGN;
   if (m == 0) return TQ_OK;

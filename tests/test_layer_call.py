@@ -18,11 +18,11 @@ def test_scratch_sizes():
     work-group to quantize), else the binding's own formula."""
     L = tq.lib()
     for n, k, r, g in ((512, 512, 16, 64), (4096, 4096, 64, 64), (4096, 14336, 64, 128), (256, 28672, 128, 64),
-                       (64, 131072, 0, 128)):
+                       (128, 65536, 64, 64), (64, 131072, 0, 128)):
         d = tq.weight_desc_init(n, k, r, g)
         for m in (1, 2, 7, 8, 9, 16, 17, 512, 513, 1000):
             got = L.tq_layer_scratch_bytes(d, m)
-            one = m <= 16 and (m == 1 or min(m, 8) * k <= 32768) and k <= 114688
+            one = m <= 16 and min(m, 8) * k <= 32768
             assert got == (0 if one else tq.layer_scratch_bytes(m, k, g)), (k, m)
     assert L.tq_layer_scratch_bytes(d, 0) == 0 and L.tq_layer_scratch_bytes(tq.WeightDesc(), 100) == 0
 
@@ -121,7 +121,7 @@ def test_only_the_saved_attributes(fake):
 @pytest.mark.parametrize("m,k,n,r,group,bf16", [
     (1, 4096, 300, 64, 64, False), (8, 4096, 300, 64, 64, True), (8, 4160, 300, 64, 64, False),
     (16, 512, 96, 16, 128, False), (16, 4160, 96, 16, 64, True), (17, 256, 100, 0, 64, False),
-    (513, 256, 100, 32, 64, False),
+    (513, 256, 100, 32, 64, False), (1, 32768, 64, 16, 64, False), (1, 40960, 64, 16, 64, False),
 ])
 def test_layer_call(m, k, n, r, group, bf16):
     """Either side of the one-launch rule, of the 4-bit / fp8 code formats, and
@@ -143,6 +143,12 @@ def test_layer_call(m, k, n, r, group, bf16):
         y = layer(x, bf16, stream=stream)
         torch.cuda.synchronize()
         assert y.dtype == ref.dtype and torch.equal(y.view(torch.int16), ref.view(torch.int16))
+    if m == 1:      # needs no scratch at any K
+        y.fill_(-1.0)
+        assert 0 == tq.lib().tq_layer(lay.desc, lay.packed.data_ptr(), x.data_ptr(), m, y.data_ptr(), 1 if bf16 else 0, None,
+                                      torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
 
 
 def stream_of(t):
