@@ -500,7 +500,10 @@ struct PKernel {
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!GA) hand_over();
     }
-    wait_vm<0>();   // the refills past the end have landed before the ring is reused
+    // all loads have landed: the refills past the end before the ring is reused,
+    // and the stage-2 operands, issued ahead of the loop, before the epilogue
+    // reads them, however short K is
+    wait_vm<0>();
   }
 
   // The stage-1 pass: H tiles of 32 tokens x 32 ranks, accumulated over all
@@ -747,11 +750,9 @@ __global__ __launch_bounds__(64 * PNW, 1) void dual_gemm_prefill_kernel(GemmArgs
     else if (wr == 0) K::template main_loop_pp<true, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc);
     else K::template main_loop_pp<false, false, GK>(P, smem, ring_lds, KG, lane, wr, wc, acc);
 
-    // Each block's loads (two or more) are behind the stage-2 operands, so all but
-    // the last two landing covers those also for the shortest K.  No test of K: a
-    // branch here cost 2 % at 8192 -> 28672, r = 128, M = 8192.
-    wait_vm<2>();
-    __syncthreads();   // every wavefront is done with the ring
+    // every wavefront is done with the ring and (main_loop_pp's last wait) has
+    // its share of the stage-2 operands in LDS
+    __syncthreads();
     if (cb + 1 < cb_end) fill(n0 + PBN);
 
     // ---- stage 2 (Q_H Q(L2)) and the single epilogue ----

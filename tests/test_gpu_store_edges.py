@@ -1,6 +1,6 @@
-"""Where the 32x32 output tiles' stores end: ragged rows and columns, odd N and a
-Y that starts on two bytes only, for each kernel that stores such tiles.  What
-lies before and after Y stays as it was."""
+"""Where the 32x32 output tiles' stores end: ragged rows and columns, even and odd
+N (odd: every second row starts on two bytes only), for each kernel that stores
+such tiles.  What lies before and after Y stays as it was."""
 import pytest
 
 import paper_2606_01556_amd as tq
@@ -68,8 +68,8 @@ def test_stores_end_at_the_tile(m, k, n, r, group, bf16):
                                        (128, 128, 128), (256, 64, 128)])
 def test_prefill_short_k(k, r, group):
     """K loops shorter than the prefill kernel's ring, over a run of three column
-    blocks (more token blocks than CUs): stage 2's operands are loaded behind the
-    ring's first fill and have to have landed by the epilogue."""
+    blocks (more token blocks than CUs): the fill repeats the last block, the
+    next column block's fill is issued ahead of the epilogue."""
     m, n = 257 * 128 - 5, 600
     print(f"prefill short k={k} r={r} group={group}", flush=True)
     gen = torch.Generator("cuda").manual_seed(k + r)
