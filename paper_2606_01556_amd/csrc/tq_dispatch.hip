@@ -1,6 +1,6 @@
 // Kernel selection for the fused layer by token count: the decode kernel for
 // m <= 16 (bound by the weight bytes; H formed in every work-group), the mid kernel
-// (32-token blocks, H formed per block) up to 512 tokens, then the large
+// (32- or 64-token blocks, H formed per block) up to 512 tokens, then the large
 // kernel (128 x 256 blocks, 16 wavefronts), or once its blocks take more
 // than one round over the CUs the prefill kernel (H shared by runs of column
 // blocks) -- for r <= 64 only where a run is long enough to carry its H pass;
@@ -15,8 +15,13 @@ namespace tq {
 // Past 512 tokens, where Y's fp32 sums may be split over K (the mid kernel's
 // plans of one or two column tiles): rounds of 32-token work-groups x (3 + rank
 // tiles + column tiles) below this many units per round of large blocks, for
-// 64- and 128-wide groups.  The line is where callers find it through
-// tq_dual_gemm_kernel, and stays; how each side runs is chosen by time below.
+// 64- and 128-wide groups.  The units are those of an earlier mid kernel; the line
+// still lies where the times cross: the mid kernel's best plan takes 0.56 of the
+// faster block kernel's time below 28 units a round, 0.85 from 28 to 34, 1.02
+// from 34 to 50 and 1.28 above (means of 4000 calls, K 512 to 16384, N 256 to
+// 16384, M 513 to 4096, r 0 to 128).  30 of 1882 calls below the line are more
+// than 10 % slower than on the large kernel, all with K <= 1536.  Between 28 and
+// 34 with 128-wide groups the exact plans below take most of what is left.
 constexpr int kLargeRound64 = 34, kLargeRound128 = 28;
 int split_units(const GemmArgs &a) {
   const int rt = a.geo.r_pad32 / 32, ct32 = a.geo.n_pad / 32, n_rb = a.ms / 32;
@@ -83,8 +88,9 @@ int64_t block_kernel_ns(const GemmArgs &a, int kernel) {
 }
 
 // Whether the mid kernel's blocks take the place of `kernel`'s (same sums).  They
-// have to be 2 % cheaper: of 1380 such calls timed, 45 % are then replaced, at
-// 0.87 of the time on average; 10 of them are slower, by 2 to 9 %.
+// have to be 2 % cheaper by the model: a third of the calls named large or
+// prefill is then replaced; all of these take 0.935 of the block kernels' time on
+// average, 55 of 2133 more than 1.02, three more than 1.05.
 bool mid_in_place(const GemmArgs &a, int kernel) {
   return a.force_kernel < 0 && a.mid_ct == 0 && 50 * dual_gemm_mid_ns(a) < 49 * block_kernel_ns(a, kernel);
 }

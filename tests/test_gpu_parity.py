@@ -193,12 +193,11 @@ def test_ragged_shapes(oracle_mod, M, K, N, r):
     (1, 1152, 96, 16),
 ])
 def test_decode_kernel_variants(oracle_mod, M, K, N, r):
-    """m <= 16 in every token layout of the decode kernel (one token, two,
-    up to 8 with two K-groups per product, up to 16), with 1, 2, 4 and 8
-    column tiles per work-group and more work-groups than CUs, odd K-group
-    counts, K at the largest size whose activation codes fit its LDS, every
-    rank-tile count, and stage-1 loops of whole ring rounds only (K-group
-    pairs a multiple of the ring depth of 10), with a tail, or a tail only."""
+    """m <= 16 in every token layout of the decode kernel (one token, two, up to
+    8, and two token blocks of up to 8 each), with 1 to 16 column tiles per
+    work-group, odd K-group counts, K at the largest size whose activation
+    codes fit its LDS (one buffer of H products there, two below), every
+    rank-tile count, and K of whole chunks only, with a tail, or a tail only."""
     say(f"decode M={M} K={K} N={N} r={r}")
     d = random_codes_layer(M, K, N, r, seed=N + r)
     g, _ = full_parity(oracle_mod, d["X"], d["W_res"], d["L1"], d["L2"])
