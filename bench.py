@@ -172,7 +172,7 @@ def trace_summary(trace_dir, title, cmd):
     rows.sort(key=lambda r: -float(r["TotalDurationNs"]))
     total = sum(float(r["TotalDurationNs"]) for r in rows)
     print(f"# {title}\n")
-    print("Command (from the repository root on the GPU box):\n")
+    print("Command (from the repository root, one MI355X):\n")
     print("```\n" + cmd + "\n```\n")
     print("| kernel | calls | avg µs | min µs | max µs | share of GPU time |")
     print("|---|---|---|---|---|---|")
@@ -216,7 +216,7 @@ def counter_summary(dirs, layer_name, m, cmd):
     cyc = per["GRBM_GUI_ACTIVE"] / XCCS          # GPU cycles of one dispatch
     wave_cyc = per.get("SQ_WAVE_CYCLES", 0.0)    # quad-cycles, summed over waves
     print(f"# SQ counters: {sym}, {HEADLINE} {layer_name} (K={layer.K}, N={layer.N}, r={layer.r}) at M={m}\n")
-    print("Commands (from the repository root on the GPU box; one rocprofv3 --pmc pass per line):\n")
+    print("Commands (from the repository root, one MI355X; one rocprofv3 --pmc pass per line):\n")
     print("```\n" + cmd + "\n```\n")
     print(f"Kernel source sha256: `{kernel_sha(kname)}`. Values: per dispatch, summed over the chip,")
     print("averaged over the dispatches of the kernel.\n")
@@ -714,18 +714,19 @@ def rank_overhead():
 def kernel_choice(group):
     """Past 512 tokens tq_dual_gemm picks the large kernel (128 x 256 blocks),
     the prefill kernel (beyond one round of blocks) or the mid kernel
-    (32-token blocks, where the large blocks would leave most CUs idle).  Times
-    each of them, forced through tq_dual_gemm_debug, beside the one it picks,
-    on LLaMA3 layer shapes in quantization groups of `group` (HIP events,
-    rotated weight copies, random-init weights).  Prints a markdown table."""
+    (32- or 64-token blocks, where the large blocks would leave most CUs idle;
+    also under the other two's names).  Times each of them, forced through
+    tq_dual_gemm_debug, beside its own choice, on LLaMA3 layer shapes in
+    quantization groups of `group` (HIP events, rotated weight copies,
+    random-init weights).  Prints a markdown table."""
     import torch
     import paper_2606_01556_amd as tq
     dev = torch.device("cuda")
     stream = torch.cuda.Stream()
     s = stream.cuda_stream
     torch.manual_seed(0)
-    print("| layer K→N | r | M | picked | large µs | prefill µs | mid µs | picked / fastest |")
-    print("|---|---|---|---|---|---|---|---|")
+    print("| layer K→N | r | M | named | block | tq_dual_gemm µs | large µs | prefill µs | mid µs | own / fastest |")
+    print("|---|---|---|---|---|---|---|---|---|---|")
     shapes = (("k/v_proj 8B", 4096, 1024), ("q/o_proj 8B", 4096, 4096), ("gate_up 8B", 4096, 14336),
               ("down 8B", 14336, 4096), ("k/v_proj 70B", 8192, 1024))
     for name, Kl, Nl in shapes:
@@ -748,16 +749,16 @@ def kernel_choice(group):
                     tq.quant_act(X, xc, xs, group, stream=s)
                 picked = tq.dual_gemm_kernel(lay.desc, m)
                 res = {}
-                for kname in ("large", "prefill", "mid"):
+                for kname in (None, "large", "prefill", "mid"):   # None: its own choice
 
                     def gemm():
                         p = copies[call[0] % ncopy]
                         call[0] += 1
                         tq.dual_gemm_debug(lay.desc, p, xc, xs, m, Y, kernel=kname, stream=s)
                     res[kname] = timed(stream, gemm, 20)
-                cell = lambda k: f"{res[k]:.1f}" if k in res else "–"
-                print(f"| {name} {Kl}→{Nl} | {rl} | {m} | {picked} | {cell('large')} | {cell('prefill')} | "
-                      f"{cell('mid')} | {res[picked] / min(res.values()):.2f} |", flush=True)
+                block = "{} x {}".format(*tq.dual_gemm_block(lay.desc, m))
+                print(f"| {name} {Kl}→{Nl} | {rl} | {m} | {picked} | {block} | {res[None]:.1f} | {res['large']:.1f} | "
+                      f"{res['prefill']:.1f} | {res['mid']:.1f} | {res[None] / min(res.values()):.2f} |", flush=True)
             del lay, copies
             torch.cuda.empty_cache()
 
