@@ -239,14 +239,20 @@ __global__ __launch_bounds__(64 * DW) void dual_gemm_decode_kernel(GemmArgs a,
   // each: with 8 + 1 the block with one token to quantize ran ahead and the
   // weights were fetched twice (8192 -> 28672 r = 0 from fp16, 9 tokens: 38 us;
   // 5 + 4: 26.5).
-  int cblk = blockIdx.x, m0 = 0;
-  if (a.m > 8) {
-    const int nwg = gridDim.x, per = nwg / 8, rem = nwg % 8, x = blockIdx.x % 8, i = blockIdx.x / 8;
-    const int logical = (x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per) + i;
-    cblk = logical / 2;
-    m0 = logical % 2 * mb;
+  // (One and two tokens are one block, and with a low-rank part go without this code:
+  // it made the scalar registers of r = 64 with eight column tiles spill 48
+  // against 11.  At r = 0 nothing spills either way, and the form with it
+  // measured 2 to 7 % faster with the weights in HBM.)
+  int cblk = blockIdx.x, m0 = 0, m = a.m;
+  if constexpr (MODE > 2 || R == 0) {
+    if (a.m > 8) {
+      const int nwg = gridDim.x, per = nwg / 8, rem = nwg % 8, x = blockIdx.x % 8, i = blockIdx.x / 8;
+      const int logical = (x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per) + i;
+      cblk = logical / 2;
+      m0 = logical % 2 * mb;
+    }
+    m = min(a.m - m0, mb);
   }
-  const int m = min(a.m - m0, mb);
   const int r = geo.r, gk = geo.gk;
   const int ct16 = geo.n_pad / 16;
   const int c0 = cblk * CT;
