@@ -75,8 +75,8 @@ int64_t block_kernel_ns(const GemmArgs &a, int kernel) {
   const int rt = a.geo.r_pad32 / 32, c = rt == 0 ? 0 : (rt <= 2 ? 1 : 2), g2 = a.geo.gk == 2;
   const int64_t kg = a.geo.k / 64;
   if (kernel == kKernelLarge) {
-    constexpr int kRound[2][3] = {{5300, 7600, 10400}, {5000, 7300, 9900}};
-    constexpr int kBlock[2][3] = {{600, 700, 885}, {466, 790, 756}};
+    constexpr int kRound[2][3] = {{6000, 7600, 10400}, {4500, 7300, 9900}};
+    constexpr int kBlock[2][3] = {{620, 700, 885}, {466, 790, 756}};
     return 900 + (m_tiles * n_tiles + 255) / 256 * (kRound[g2][c] + kg * kBlock[g2][c]);
   }
   // launch, column block, H pass and column block per K block

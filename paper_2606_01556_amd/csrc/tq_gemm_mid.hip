@@ -595,9 +595,9 @@ MidPlan mid_exact_cost(const GemmArgs &a, int tb, int ct) {
   const int rt = a.geo.r_pad32 / 32, c = rt == 0 ? 0 : (rt <= 2 ? 1 : 2);
   constexpr int kNs[2][2][3][3] = {
       {{{2260, 2370, 105}, {2200, 4280, 162}, {1900, 5620, 188}},
-       {{1840, 4010, 305}, {1520, 6320, 293}, {2380, 7360, 292}}},
+       {{1840, 4500, 285}, {1520, 6320, 293}, {2380, 7360, 292}}},
       {{{2250, 2840, 92}, {2120, 4490, 132}, {1840, 5450, 149}},
-       {{1510, 4460, 260}, {1820, 6410, 250}, {2320, 7060, 251}}}};
+       {{1510, 4000, 245}, {1820, 6410, 250}, {2320, 7060, 251}}}};
   const int *t = kNs[a.geo.gk - 1][tb - 1][c];
   return MidPlan{tb, ct, t[0] + mid_rounds(a, tb, ct) * (t[1] + (int64_t)t[2] * (a.geo.k / 64))};
 }
