@@ -53,7 +53,9 @@ int choose_kernel(const GemmArgs &a) {
   // With 128-wide groups the large kernel chains two dependent products per H
   // tile in its main loop, and the prefill kernel applies half the scale
   // products per K block: the prefill kernel wins past one round of blocks
-  // at every rank but 0.
+  // at every rank but 0 -- there the large kernel took 273 us and it 288 (4096 ->
+  // 14336, M = 4096) when the line was drawn, 266 and 233 now; the name stays
+  // where callers find it, and the two return the same bits.
   const bool prefill_wins = a.geo.gk == 1 ? a.geo.r_pad32 > 64 || long_run : a.geo.r_pad32 > 0;
   const bool large = blocks <= 256 || !prefill_wins;
   // few large blocks leave most CUs idle

@@ -41,20 +41,30 @@
 // four per lane) are rescaled.  9 to 16 tokens are two token blocks of half
 // of them each in the grid.
 //
-// What bounds it.  At these sizes a CU's vector ALU (a 4-bit operand takes 12
-// integer instructions of four cycles to expand, three quarters of a tile's
-// work) and its load path (64 bytes a clock: 2.3 MB per CU for 28672 -> 8192,
-// r = 128), neither hidden by the other for long behind the chunk's barrier.
-// Before, each rank tile of H was one wavefront's own chain, ~48 instructions
-// per pair one after the other, and its wavefront alone set the time.  us per
-// launch (one token unless said), before -> after: 4096 -> 4096, r = 64 10.8 ->
-// 8.5; 14336 -> 4096, r = 64 22.6 -> 15.6; 28672 -> 8192, r = 128 59.5 -> 52;
-// 8192 -> 28672, r = 128 5 tokens 45 -> 38; 14336 -> 4096, r = 64 8 tokens 41 ->
-// 22.  Tried and not kept: two pairs of a wavefront between barriers (no
+// What bounds it.  No unit alone.  For 28672 -> 8192, r = 128, one token, the
+// vector ALU is active 45 % of a SIMD's cycles (a 4-bit operand takes 12 integer
+// instructions of four cycles to expand, three quarters of a tile's work), a CU's
+// load path about 40 % (2.3 MB), the matrix cores 12 %; the rest is loads and
+// chunk barriers waited for.  Before, each rank tile of H was one wavefront's own
+// chain, ~48 instructions per pair one after the other, and its wavefront alone
+// set the time.  us per launch from codes, weights in the memory-side cache (from
+// HBM), one token unless said, before -> now: 4096 -> 4096, r = 64 9.4 -> 8.1 (11.4
+// -> 9.5); 14336 -> 4096, r = 64 20.4 -> 14.9 (23.9 -> 18.5); 28672 -> 8192, r = 128,
+// fp16 in 55.9 -> 51.1; 8192 -> 28672, r = 128 5 tokens 34.8 -> 28.9 (40.6 -> 35.0);
+// 14336 -> 4096, r = 64 8 tokens 38.1 -> 21.6.  Slower than before: one and two
+// tokens, N > 16384, with the weights in the cache (8192 -> 28672, r = 128 25.2 ->
+// 27.2; from HBM 37.3 -> 35.6; 1280 -> 28672, r = 32 7.3 -> 8.2, from HBM even); 9 to
+// 16 tokens, N > 16384, at K <= 1280 (10.7 -> 11.4 at 1280, r = 64), and from HBM at
+// K >= 8192 with r <= 64 (14336 -> 28672, r = 64 57.7 -> 64.3; r = 128 faster): there
+// two token blocks of sixteen tiles fetch more than the one of eight did.
+// Tried and not kept: two pairs of a wavefront between barriers (no
 // change), non-temporal weight or L1 loads (2-20 % slower), the chain after the
 // products instead of ahead of them (8 % slower), a 16-token layout of two
-// products per tile (44 us where two token blocks take 27: its products and
-// codes fill the LDS, so nothing is double-buffered).
+// products per tile (44 us where two token blocks take 23: its products and
+// codes fill the LDS, so nothing is double-buffered), three or four chunks of
+// operands in flight (2-10 % slower: longer code), a test for pairs past K
+// around the products (3-5 % slower on long K), and the kernel of before where N >
+// 16384 (faster with the weights in the cache, 5-9 % slower from HBM).
 
 #include <type_traits>
 
