@@ -57,6 +57,9 @@ def test_wide_work_groups(oracle_mod, M, K, N, r, group):
     (12, 64, 17000, 64, 64),
     (16, 1280, 16500, 0, 128),
     (9, 384, 16500, 128, 64),
+    # either side of the K from which LDS holds one buffer of H products, not two
+    (1, 103168, 32, 128, 64), (1, 103232, 32, 128, 64), (2, 53568, 32, 128, 64),
+    (8, 21120, 32, 128, 64), (8, 21184, 32, 128, 64),
 ])
 def test_wavefronts_per_pair(oracle_mod, M, K, N, r, group):
     """Short and long K at each way a pair's tiles are shared out: H bit-exact,
