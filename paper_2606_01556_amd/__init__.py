@@ -131,7 +131,7 @@ def _other_stream(stream, handle, device):
     """`stream` (a torch stream or a hipStream_t, `handle` its hipStream_t) as a
     torch stream of `device`, or None where it is the current one there."""
     import torch
-    if handle == torch.cuda.current_stream(device).cuda_stream:
+    if handle == torch._C._cuda_getCurrentRawStream(device.index):
         return None
     if isinstance(stream, torch.cuda.Stream):
         return stream

@@ -99,7 +99,10 @@ bool mid_in_place(const GemmArgs &a, int kernel) {
 
 int dual_gemm_block(const GemmArgs &a) {
   const int kernel = choose_kernel(a);
-  if (kernel == kKernelDecode) return dual_gemm_decode_block(a);
+  if (kernel == kKernelDecode) {   // (a token block's room for 8 tokens, or half of 9 to 16)
+    const int b = dual_gemm_decode_block(a);
+    return std::min(a.m, b >> 16) << 16 | (b & 0xffff);
+  }
   const bool exact = kernel != kKernelMid;
   return !exact || mid_in_place(a, kernel) ? dual_gemm_mid_block(a, exact) : 128 << 16 | 256;
 }

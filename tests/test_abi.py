@@ -338,7 +338,7 @@ def test_block_choice(L):
     a call of more than a second by it keeps its large blocks."""
     block = lambda n, k, r, m, group=64: tq.dual_gemm_block(tq.weight_desc_init(n, k, r, group), m)
     assert [block(n, 4096, 64, 1) for n in (4096, 4097, 8192, 16384, 16416, 32800)] == \
-        [(8, 16), (8, 32), (8, 32), (8, 64), (8, 128), (8, 256)]
+        [(1, 16), (1, 32), (1, 32), (1, 64), (1, 128), (1, 256)]
     assert block(4096, 4096, 64, 9) == (5, 32) and block(4096, 4096, 64, 16) == (8, 32)
     assert block(4096, 4096, 64, 17)[0] == 32 and block(12288, 4096, 64, 256) == (64, 192)
     assert block(5001, 2880, 16, 777) == (64, 224)
