@@ -455,7 +455,8 @@ class Layer:
         if desc.k != k or desc.n != n:
             raise ValueError(f"desc: {desc.n} x {desc.k}, the layer is {n} x {k}")
         st = _stream(stream)
-        nscratch = _layer_scratch(m, k, desc.group)
+        # past 16 tokens it is always two launches, and any m may come
+        nscratch = (layer_scratch_bytes if m > 16 else _layer_scratch)(m, k, desc.group)
         dtype = torch.bfloat16 if bf16 else None
         new = (x if type(x) is torch.Tensor else x.as_subclass(torch.Tensor)).new_empty   # Y is a plain tensor
         other = None if stream is None else _other_stream(stream, st, x.device)
