@@ -50,7 +50,7 @@
 // set the time.  us per launch from codes, weights in the memory-side cache (from
 // HBM), one token unless said, before -> now: 4096 -> 4096, r = 64 9.4 -> 8.1 (11.4
 // -> 9.5); 14336 -> 4096, r = 64 20.4 -> 14.9 (23.9 -> 18.5); 28672 -> 8192, r = 128,
-// fp16 in 55.9 -> 51.1; 8192 -> 28672, r = 128 5 tokens 34.8 -> 28.9 (40.6 -> 35.0);
+// fp16 in 55.9 -> 49.8; 8192 -> 28672, r = 128 5 tokens 34.8 -> 28.9 (40.6 -> 35.0);
 // 14336 -> 4096, r = 64 8 tokens 38.1 -> 21.6.  Slower than before: one and two
 // tokens, N > 16384, with the weights in the cache (8192 -> 28672, r = 128 25.2 ->
 // 27.2; from HBM 37.3 -> 35.6; 1280 -> 28672, r = 32 7.3 -> 8.2, from HBM even); 9 to
