@@ -340,6 +340,8 @@ def test_block_choice(L):
     assert [block(n, 4096, 64, 1) for n in (4096, 4097, 8192, 16384, 16416, 32800)] == \
         [(1, 16), (1, 32), (1, 32), (1, 64), (1, 128), (1, 256)]
     assert block(4096, 4096, 64, 9) == (5, 32) and block(4096, 4096, 64, 16) == (8, 32)
+    assert [block(n, 4096, 64, 16) for n in (16384, 16385, 24576, 24577)] == [(8, 128), (8, 192), (8, 192), (8, 256)]
+    assert block(49152, 4096, 64, 3) == (3, 192) and block(49152, 4096, 64, 2) == (2, 256)
     assert block(4096, 4096, 64, 17)[0] == 32 and block(12288, 4096, 64, 256) == (64, 192)
     assert block(5001, 2880, 16, 777) == (64, 224)
     assert block(4096, 4096, 64, 2048) == (128, 256) and block(28672, 8192, 128, 8192) == (128, 256)

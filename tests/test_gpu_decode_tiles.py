@@ -1,5 +1,6 @@
-"""GPU parity of the decode kernel's wide work-groups (sixteen column tiles,
-four wavefronts per pair of K blocks) and of its two token blocks."""
+"""GPU parity of the decode kernel's wide work-groups (twelve and sixteen column
+tiles, four or eight wavefronts per pair of K blocks), of the ways a pair's
+tiles are shared out, and of its two token blocks."""
 import numpy as np
 import pytest
 
@@ -27,6 +28,11 @@ def _gpu():
     (9, 1088, 16500, 64, 64),      # a second token block of one token
     (16, 512, 16400, 128, 128),
     (12, 320, 20000, 0, 64),
+    (16, 640, 24576, 8, 64),       # the last N of twelve tiles, and the first of sixteen
+    (9, 384, 24577, 128, 64),
+    (16, 1280, 24600, 0, 128),
+    (12, 64, 24600, 64, 64),
+    (5, 192, 49100, 128, 64),      # one token block of twelve tiles
 ])
 def test_wide_work_groups(oracle_mod, M, K, N, r, group):
     """More column tiles (times token blocks) than eight per CU: codes and fp16
@@ -54,9 +60,9 @@ def test_wide_work_groups(oracle_mod, M, K, N, r, group):
     (7, 1152, 300, 64, 128),
     # two token blocks, eight wavefronts per pair: a single K block, whole and
     # broken chunks of two pairs
-    (12, 64, 17000, 64, 64),
-    (16, 1280, 16500, 0, 128),
-    (9, 384, 16500, 128, 64),
+    (12, 64, 25000, 64, 64),
+    (16, 1280, 24600, 0, 128),
+    (9, 384, 24800, 128, 64),
     # either side of the K from which LDS holds one buffer of H products, not two
     (1, 103168, 32, 128, 64), (1, 103232, 32, 128, 64), (2, 53568, 32, 128, 64),
     (8, 21120, 32, 128, 64), (8, 21184, 32, 128, 64),
