@@ -52,8 +52,9 @@
 // -> 9.5); 14336 -> 4096, r = 64 20.4 -> 14.9 (23.9 -> 18.5); 28672 -> 8192, r = 128,
 // fp16 in 55.9 -> 49.8; 8192 -> 28672, r = 128 5 tokens 34.8 -> 28.9 (40.6 -> 35.0);
 // 14336 -> 4096, r = 64 8 tokens 38.1 -> 21.6.  Slower than before: one and two
-// tokens, N > 16384, with the weights in the cache (8192 -> 28672, r = 128 25.2 ->
-// 27.2; from HBM 37.3 -> 35.6; 1280 -> 28672, r = 32 7.3 -> 8.2, from HBM even); 9 to
+// tokens with the weights in the cache, N > 24576 (8192 -> 28672, r = 128 25.2 ->
+// 27.2; from HBM 37.3 -> 35.6) and N > 16384 at K ~ 1280 (1280 -> 28672, r = 32 7.3 ->
+// 8.2, from HBM even); 9 to
 // 16 tokens, N > 24576, at K <= 1280 (10.7 -> 11.4 at 1280, r = 64), and from HBM at
 // K >= 8192 with r <= 64 (14336 -> 28672, r = 64 57.7 -> 64.3; r = 128 faster): there
 // two token blocks of sixteen tiles fetch more than the one of eight did.
@@ -103,10 +104,11 @@ constexpr int split_cw(int ct, int s) { return ct > s ? ct / s : 1; }      // co
 // most that still divide the tiles.
 constexpr int split_min(int mode, int r, int ct) {
   if (ct >= 12 || (mode > 2 && r >= 4 && r + ct > 10)) return 4;
-  if (r + ct > (mode == 1 ? 10 : (mode == 2 ? 8 : 5)) || ct == 8) return 2;
+  if (r + ct > (mode == 1 ? 10 : (mode == 2 ? 8 : 5)) || ct == 8 || ct == 6) return 2;
   return mode > 2 && r == 4 ? 2 : 1;
 }
 constexpr int split_max(int mode, int r, int ct) {
+  if (ct == 6) return 2;   // (three tiles each)
   const int tiles = r > ct ? r : ct, s = ct == 16 ? 8 : (tiles < 4 ? tiles : 4);
   return s > split_min(mode, r, ct) ? s : split_min(mode, r, ct);
 }
@@ -865,25 +867,33 @@ hipError_t launch_decode_ct(const GemmArgs &a, const uint16_t *xh, hipStream_t s
 
 template <int MODE, int R>
 hipError_t launch_decode_r(int ct, const GemmArgs &a, const uint16_t *xh, hipStream_t s) {
+  if constexpr (MODE <= 2) {
+    if (ct == 6) return launch_decode_ct<MODE, R, 6>(a, xh, s);
+  } else {
+    if (ct == 12) return launch_decode_ct<MODE, R, 12>(a, xh, s);
+  }
   switch (ct) {
     case 1: return launch_decode_ct<MODE, R, 1>(a, xh, s);
     case 2: return launch_decode_ct<MODE, R, 2>(a, xh, s);
     case 4: return launch_decode_ct<MODE, R, 4>(a, xh, s);
     case 8: return launch_decode_ct<MODE, R, 8>(a, xh, s);
-    case 12:
-      if constexpr (MODE > 2) return launch_decode_ct<MODE, R, 12>(a, xh, s);
     default: return launch_decode_ct<MODE, R, 16>(a, xh, s);
   }
 }
 
 // The fewest 16-column tiles per work-group that keep the grid within one
-// work-group per CU; from three tokens on also twelve, where sixteen would leave
-// up to half of the CUs without one: 14336 -> 16416, 16 tokens, from HBM r = 0
-// 47.7 -> 38.3 us (the kernel of before 36.8), r = 64 59.5 -> 49.1 (53.4).  (One and two
-// tokens have no twelve: their sixteen, N > 32768, are far ahead of before.)
+// work-group per CU.  Where a power of two would leave up to half of the CUs
+// without one, also twelve from three tokens on (14336 -> 16416, 16 tokens, from
+// HBM r = 0 47.7 -> 38.3 us, the kernel of before 36.8; r = 64 59.5 -> 49.1, 53.4) and
+// six for one and two (8192 -> 18944, r = 128, one token 22.9 -> 21.3 us, before 21.9;
+// from HBM 32.1 -> 29.8, 33.6) -- these from K = 2048, since six are shared by two
+// wavefronts only and a short K is faster shared out wider (1280 -> 18944, r = 128
+// 8.9 against 9.5 us).  Sixteen for one and two tokens, N > 32768, are far ahead
+// of before as they are.
 int decode_tiles(const GemmArgs &a) {
   const int tiles16 = a.geo.n_pad / 16 * ((a.m + 7) / 8);
   if (a.m > 2 && tiles16 > 2048 && tiles16 <= 3072) return 12;
+  if (a.m <= 2 && tiles16 > 1024 && tiles16 <= 1536 && a.geo.k >= 2048) return 6;
   return tiles16 <= 256 ? 1 : (tiles16 <= 512 ? 2 : (tiles16 <= 1024 ? 4 : (tiles16 <= 2048 ? 8 : 16)));
 }
 

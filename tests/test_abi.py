@@ -338,7 +338,10 @@ def test_block_choice(L):
     a call of more than a second by it keeps its large blocks."""
     block = lambda n, k, r, m, group=64: tq.dual_gemm_block(tq.weight_desc_init(n, k, r, group), m)
     assert [block(n, 4096, 64, 1) for n in (4096, 4097, 8192, 16384, 16416, 32800)] == \
-        [(1, 16), (1, 32), (1, 32), (1, 64), (1, 128), (1, 256)]
+        [(1, 16), (1, 32), (1, 32), (1, 64), (1, 96), (1, 256)]
+    assert [block(n, k, 64, m) for n, k, m in ((16384, 2048, 1), (16385, 2048, 2), (24576, 2048, 2), (24577, 2048, 2),
+                                               (16416, 1984, 1), (16416, 2048, 3))] == \
+        [(1, 64), (2, 96), (2, 96), (2, 128), (1, 128), (3, 128)]
     assert block(4096, 4096, 64, 9) == (5, 32) and block(4096, 4096, 64, 16) == (8, 32)
     assert [block(n, 4096, 64, 16) for n in (16384, 16385, 24576, 24577)] == [(8, 128), (8, 192), (8, 192), (8, 256)]
     assert block(49152, 4096, 64, 3) == (3, 192) and block(49152, 4096, 64, 2) == (2, 256)

@@ -1,5 +1,5 @@
-"""GPU parity of the decode kernel's wide work-groups (twelve and sixteen column
-tiles, four or eight wavefronts per pair of K blocks), of the ways a pair's
+"""GPU parity of the decode kernel's wide work-groups (six, twelve and sixteen
+column tiles, four or eight wavefronts per pair of K blocks), of the ways a pair's
 tiles are shared out, and of its two token blocks."""
 import numpy as np
 import pytest
@@ -33,6 +33,11 @@ def _gpu():
     (16, 1280, 24600, 0, 128),
     (12, 64, 24600, 64, 64),
     (5, 192, 49100, 128, 64),      # one token block of twelve tiles
+    # one and two tokens: six tiles from K = 2048 on, an odd number of K blocks
+    (1, 2048, 16400, 128, 64),
+    (2, 2368, 20001, 32, 64),
+    (2, 2048, 24576, 16, 128),
+    (1, 2112, 24560, 0, 64),
 ])
 def test_wide_work_groups(oracle_mod, M, K, N, r, group):
     """More column tiles (times token blocks) than eight per CU: codes and fp16
